@@ -16,6 +16,7 @@
 #include "sim_kernel.hpp"
 #include "sim_shared.hpp"
 #include "sim_launch.hpp"
+#include "sim_lean.hpp"
 #include "sim_internal.hpp"
 
 namespace as_host {
@@ -88,16 +89,16 @@ hipError_t launch_lds_any(int W, int gpl, int smax, bool seg, const KArgs& a, si
   }
 }
 
-hipError_t launch_shared_any(int W, int smax, bool usig, const KArgs& a, size_t lds, hipStream_t s,
-                             bool stats) {
+hipError_t launch_lean_any(LeanKind kind, int W, int smax, const KArgs& a, int jw, int64_t blocks, int waves,
+                           size_t lds, hipStream_t s) {
   switch (W) {
-    case 1: return as_host::launch_shared<1>(smax, usig, stats, a, lds, s);
-    case 2: return as_host::launch_shared<2>(smax, usig, stats, a, lds, s);
-    case 4: return as_host::launch_shared<4>(smax, usig, stats, a, lds, s);
-    case 8: return as_host::launch_shared<8>(smax, usig, stats, a, lds, s);
-    case 16: return as_host::launch_shared<16>(smax, usig, stats, a, lds, s);
-    case 32: return as_host::launch_shared<32>(smax, usig, stats, a, lds, s);
-    default: return as_host::launch_shared<64>(smax, usig, stats, a, lds, s);
+    case 1: return as_host::launch_lean<1>(kind, smax, a, jw, blocks, waves, lds, s);
+    case 2: return as_host::launch_lean<2>(kind, smax, a, jw, blocks, waves, lds, s);
+    case 4: return as_host::launch_lean<4>(kind, smax, a, jw, blocks, waves, lds, s);
+    case 8: return as_host::launch_lean<8>(kind, smax, a, jw, blocks, waves, lds, s);
+    case 16: return as_host::launch_lean<16>(kind, smax, a, jw, blocks, waves, lds, s);
+    case 32: return as_host::launch_lean<32>(kind, smax, a, jw, blocks, waves, lds, s);
+    default: return as_host::launch_lean<64>(kind, smax, a, jw, blocks, waves, lds, s);
   }
 }
 
@@ -112,6 +113,39 @@ int simd_count() {
     cache[dev] = prop.multiProcessorCount * 4;
   }
   return cache[dev];
+}
+
+// Jobs per wavefront of a shared trace (at most 64 / W): as few as leave one
+// wavefront per SIMD, since jobs that share a wavefront stage the requests of
+// all of them and a second wavefront on a SIMD slows the first.
+int lean_jobs_per_wave(int W, int64_t J) {
+  const int64_t need = (J + simd_count() - 1) / simd_count();
+  return (int)std::max<int64_t>(1, std::min<int64_t>(64 / W, need));
+}
+
+// Wavefronts per workgroup: as many as put every workgroup on a compute unit
+// of its own, up to the four that its SIMDs run side by side (two workgroups
+// of two wavefronts can share two SIMDs and leave two idle: 777 wavefronts of
+// 32 lanes and 2 stages took 10.8 ms so, 7.4 ms in workgroups of four),
+// fewer where their LDS does not fit.
+int lean_waves_per_block(int64_t waves, int W, const KArgs& a, int smax, bool stats) {
+  const int64_t cus = compute_units();
+  int w = waves > 2 * cus ? 4 : waves > cus ? 2 : 1;
+  while (w > 1 && as_dev::lean_lds_bytes(W, a.M, pow2ceil(a.C), smax, stats, w) > shared_lds_limit()) w /= 2;
+  return w;
+}
+
+// Wavefronts of J jobs (K scales per placement) at jw jobs per wavefront.
+int64_t lean_wave_count(int64_t J, int64_t K, int jw) { return K * ((J / K + jw - 1) / jw); }
+
+// Which calls the group-per-lane kernels take, by their stage-latency tables:
+// the sizes these calls have always been taken up to (the table, the model
+// records of four wavefronts and a staged chunk of 2048, or of four times 256,
+// requests in a workgroup's LDS); larger ones go to the general kernel, or are
+// refused, as before.  The kernels themselves need less.
+bool lean_takes(const KArgs& a, int smax, int chunk = 2048) {
+  const size_t records = (size_t)as_dev::kWaves * a.M * ((size_t)1 << as_dev::rec_shift(smax));
+  return records + (size_t)a.M * pow2ceil(a.C) * smax * 8 + (size_t)chunk * 20 <= shared_lds_limit();
 }
 
 // Lanes per job W and groups per lane GPL (W * GPL >= G, powers of two).
@@ -304,39 +338,16 @@ __global__ void validate_kernel(const double* t, const int32_t* model, int64_t n
   if (bad) atomicOr(flags, bad);
 }
 
-// Fill p[0, n) with v (per-request output rows before a shared-trace launch);
-// nothing when gate is set and *gate == 0.
-__global__ void fill_f64(double* __restrict__ p, int64_t n, double v, const int32_t* gate) {
-  if (gate && *gate == 0) return;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = v;
-}
-
-// Fill the per-request output rows of segmented jobs with -2 over
-// [0, min(segment length, finish_stride)) (the rest stays untouched).
-__global__ void fill_seg_rows(const KArgs a) {
-  const int64_t total = (int64_t)a.n_finish * a.finish_stride;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int f = (int)(i / a.finish_stride);
-    const int64_t k = i % a.finish_stride;
-    int p = 0;
-    double sigma = 0.0;
-    int64_t begin = 0, len = 0;
-    as_dev::seg_job(a, a.finish_jobs[f], p, sigma, begin, len);
-    if (k < len) a.out_finish[i] = -2.0;
-  }
-}
-
-// Statistics launch of the shared-trace kernel (one SLO scale, no per-request
-// rows): AS_E_LIMITS when its tables do not fit in a workgroup's LDS.
+// Statistics launch of the shared-trace kernel (no per-request rows):
+// AS_E_LIMITS when its tables do not fit in a workgroup's LDS.
 int run_shared_stats(KArgs& a, int smax, hipStream_t stream) {
-  const int Ws = pow2ceil(a.G);
-  const size_t lds = as_dev::shared_lds_bytes(a.M, pow2ceil(a.C), smax) + as_dev::shared_stats_lds_bytes(Ws, a.M);
-  if (!use_shared_path() || a.K != 1 || a.n_finish != 0 || lds > shared_lds_limit())
-    return AS_E_LIMITS;
-  const hipError_t e = launch_shared_any(Ws, smax, true, a, lds, stream, true);
+  const int W = pow2ceil(a.G), jw = lean_jobs_per_wave(W, a.J);
+  const int64_t nw = lean_wave_count(a.J, a.K, jw);
+  const int waves = lean_waves_per_block(nw, W, a, smax, true);
+  const size_t lds = as_dev::lean_lds_bytes(W, a.M, pow2ceil(a.C), smax, true, waves);
+  if (!use_shared_path() || a.n_finish != 0 || lds > shared_lds_limit()) return AS_E_LIMITS;
+  const hipError_t e =
+      launch_lean_any(LeanKind::kStats, W, smax, a, jw, (nw + waves - 1) / waves, waves, lds, stream);
   if (e != hipSuccess) return fail(AS_E_HIP, "kernel launch failed: %s", hipGetErrorString(e));
   return ok();
 }
@@ -354,21 +365,22 @@ int run_shared_multi(const KArgs& a, void* dev_args, const ShapeJobs* sh, int n,
   size_t lds = 0;
   as_dev::MultiSegs ms;
   std::memset(&ms, 0, sizeof ms);
-  int64_t blocks = 0;
+  int64_t blocks = 0, all = 0;
+  for (int i = 0; i < n; ++i) all += sh[i].v.J;
+  const int waves = 4;
   for (int i = 0; i < n; ++i) {
     const int W = sh[i].W, sm = sh[i].smax;
     if (W < 1 || W > 64 || (W & (W - 1)) != 0 || sh[i].v.G > W || (sm != 1 && sm != 2 && sm != 4 && sm != 8))
       return AS_E_LIMITS;
     if (sh[i].v.J <= 0) continue;
+    if (!lean_takes(a, sm)) return AS_E_LIMITS;
     if (!stats) {
       KArgs ak = a;
       ak.J = sh[i].v.J;
       ak.G = sh[i].v.G;
       if (want_spec(ak, sm) && spec_takes(ak, sm)) return AS_E_LIMITS;
     }
-    const size_t l = as_dev::shared_lds_bytes(a.M, pow2ceil(a.C), sm) +
-                     (stats ? as_dev::shared_stats_lds_bytes(W, a.M) : 0);
-    lds = std::max(lds, l);
+    lds = std::max(lds, as_dev::lean_lds_bytes(W, a.M, pow2ceil(a.C), sm, stats, waves));
     as_dev::ShapeSeg& g = ms.s[ms.n++];
     int wl = 0, sl = 0;
     while ((1 << wl) < W) ++wl;
@@ -377,13 +389,13 @@ int run_shared_multi(const KArgs& a, void* dev_args, const ShapeJobs* sh, int n,
     g.sl = sl;
     g.block0 = blocks;
     g.v = sh[i].v;
-    const int64_t slots = (int64_t)(64 / W) * as_dev::kWaves;
-    blocks += (sh[i].v.J + slots - 1) / slots;
+    g.v.jw = lean_jobs_per_wave(W, all);
+    blocks += (lean_wave_count(g.v.J, 1, g.v.jw) + waves - 1) / waves;
   }
   if (lds > shared_lds_limit() || blocks > kMultiMaxBlocks) return AS_E_LIMITS;
   if (ms.n == 0) return ok();
   hipError_t e = hipMemcpyAsync(dev_args, &a, sizeof(KArgs), hipMemcpyHostToDevice, stream);
-  if (e == hipSuccess) e = launch_shared_multi(stats, static_cast<const KArgs*>(dev_args), ms, blocks, lds, stream);
+  if (e == hipSuccess) e = launch_shared_multi(stats, static_cast<const KArgs*>(dev_args), ms, blocks, waves, lds, stream);
   if (e != hipSuccess) return fail(AS_E_HIP, "kernel launch failed: %s", hipGetErrorString(e));
   return ok();
 }
@@ -394,21 +406,15 @@ int run_shared_multi(const KArgs& a, void* dev_args, const ShapeJobs* sh, int n,
 // takes the call (AS_OK) or not (AS_E_LIMITS), without launching.
 int run_trace_kernels(KArgs& a, int W, int smax, hipStream_t stream, bool only_check) {
   const int64_t J = a.J;
-  const size_t lds_shared = as_dev::shared_lds_bytes(a.M, pow2ceil(a.C), smax);
-  if (use_shared_path() && lds_shared <= shared_lds_limit()) {
+  const int Ws = pow2ceil(a.G), jw = lean_jobs_per_wave(Ws, J);
+  // the jobs, and those with a per-request row once more
+  const int64_t nw = lean_wave_count(J, a.K, jw) + (a.n > 0 ? a.n_finish : 0);
+  const int waves = lean_waves_per_block(nw, Ws, a, smax, false);
+  const size_t lds_shared = as_dev::lean_lds_bytes(Ws, a.M, pow2ceil(a.C), smax, false, waves);
+  if (use_shared_path() && lean_takes(a, smax) && lds_shared <= shared_lds_limit()) {
     if (only_check) return AS_OK;
-    const int Ws = pow2ceil(a.G);
-    hipError_t e = hipSuccess;
-    if (a.n_finish > 0 && a.n > 0) {
-      // rows start at -2 (no hosting group); the kernel writes the others
-      const int64_t cells = (int64_t)a.n_finish * a.n;
-      const int64_t blocks = std::min<int64_t>((cells + 255) / 256, 8192);
-      hipLaunchKernelGGL(fill_f64, dim3((unsigned)blocks), dim3(256), 0, stream, a.out_finish,
-                         cells, -2.0, a.gate);
-      if ((e = hipGetLastError()) != hipSuccess)
-        return fail(AS_E_HIP, "kernel launch failed: %s", hipGetErrorString(e));
-    }
-    e = launch_shared_any(Ws, smax, a.K == 1, a, lds_shared, stream, false);
+    const hipError_t e = launch_lean_any(LeanKind::kShared, Ws, smax, a, jw, (nw + waves - 1) / waves, waves,
+                                         lds_shared, stream);
     if (e != hipSuccess) return fail(AS_E_HIP, "kernel launch failed: %s", hipGetErrorString(e));
     return ok();
   }
@@ -680,18 +686,14 @@ int as_simulate_jobs(const double* t, const int32_t* model, const int64_t* seg_o
   a.out_digest = out_digest;
   a.finish_stride = finish_stride;
   hipStream_t s = (hipStream_t)stream;
-  // more than 32 groups: one job per wavefront with the shared-trace request
-  // loop (the requests of a wavefront are one job's)
-  const size_t lds_seg = as_dev::seg_lds_bytes(a.M, pow2ceil(a.C), smax);
-  if (use_shared_path() && pow2ceil(a.G) == 64 && lds_seg <= shared_lds_limit()) {
+  // one job per wavefront (the requests of a wavefront are one job's)
+  const int Ws = pow2ceil(a.G);
+  const size_t lds_seg = as_dev::lean_lds_bytes(Ws, a.M, pow2ceil(a.C), smax, false, as_dev::kWaves);
+  int GPL = 1;
+  const bool general = choose_shape(a.G, n_jobs, true, a.M, a.C, smax, W, GPL);
+  if (use_shared_path() && (general || (Ws == 64 && lean_takes(a, smax, 1024))) && lds_seg <= shared_lds_limit()) {
     hipError_t e = hipSuccess;
-    if (a.n_finish > 0 && finish_stride > 0) {
-      const int64_t cells = (int64_t)a.n_finish * finish_stride;
-      const int64_t blocks = std::min<int64_t>((cells + 255) / 256, 8192);
-      hipLaunchKernelGGL(fill_seg_rows, dim3((unsigned)blocks), dim3(256), 0, s, a);
-      if ((e = hipGetLastError()) != hipSuccess)
-        return fail(AS_E_HIP, "kernel launch failed: %s", hipGetErrorString(e));
-    }
+    const int64_t n_rows = finish_stride > 0 ? a.n_finish : 0;
     // Jobs longest first.  With more jobs than seg_waves_per_simd()
     // wavefronts per SIMD, that many wavefronts take them in turn (each
     // compute unit holds that many workgroups of one wavefront per SIMD: the
@@ -700,7 +702,8 @@ int as_simulate_jobs(const double* t, const int32_t* model, const int64_t* seg_o
     // jobs are too many for the sort or its array cannot be allocated.
     const int wps = as_dev::seg_waves_per_simd();
     const int64_t queue_blocks = as_dev::seg_queue_blocks(wps);
-    int64_t blocks = (n_jobs + as_dev::kWaves - 1) / as_dev::kWaves;
+    int waves = lean_waves_per_block(n_jobs + n_rows, Ws, a, smax, false);
+    int64_t blocks = (n_jobs + n_rows + waves - 1) / waves;
     size_t lds = lds_seg;
     int32_t* order = nullptr;
     if (n_jobs >= 2 && n_jobs <= as_dev::kOrderMaxJobs &&
@@ -714,6 +717,7 @@ int as_simulate_jobs(const double* t, const int32_t* model, const int64_t* seg_o
       a.order = order;
       if (queue) {
         a.next_slot = order + n_jobs;
+        waves = as_dev::kWaves;
         blocks = queue_blocks;
         const size_t per_cu = 160 * 1024;  // LDS of a compute unit
         const size_t cap = per_cu / (size_t)(wps + 1) + 1024;
@@ -722,14 +726,13 @@ int as_simulate_jobs(const double* t, const int32_t* model, const int64_t* seg_o
     } else {
       (void)hipGetLastError();
     }
-    e = as_host::launch_seg64(smax, a, blocks, lds, s);
+    e = launch_lean_any(LeanKind::kSeg, Ws, smax, a, 1, blocks, waves, lds, s);
     const hipError_t ef = order ? hipFreeAsync(order, s) : hipSuccess;
     if (e != hipSuccess) return fail(AS_E_HIP, "kernel launch failed: %s", hipGetErrorString(e));
     if (ef != hipSuccess) return fail(AS_E_HIP, "order release failed: %s", hipGetErrorString(ef));
     return ok();
   }
-  int GPL = 1;
-  if (!choose_shape(a.G, n_jobs, true, a.M, a.C, smax, W, GPL))
+  if (!general)
     return fail(AS_E_LIMITS, "stage-latency tables (%d models x %d configs x %d stages) do not fit in LDS",
                 a.M, a.C, smax);
   const size_t lds = lds_bytes(W, smax, true, a.M, a.C);

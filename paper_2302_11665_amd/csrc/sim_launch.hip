@@ -3,7 +3,7 @@
 
 #include "sim_kernel.hpp"
 #include "sim_launch.hpp"
-#include "sim_shared.hpp"
+#include "sim_lean.hpp"
 
 #ifndef AS_W
 #error "compile with -DAS_W=<lanes per job>"
@@ -35,20 +35,18 @@ hipError_t lds_s(int smax, const KArgs& a, size_t lds, hipStream_t s) {
   }
 }
 
-template <int W, int SMAX>
-hipError_t shared_t(bool usig, bool stats, const KArgs& a, size_t lds, hipStream_t s) {
-  constexpr int slots = (64 / W) * as_dev::kWaves;
-  const int grid = (a.J + slots - 1) / slots;
-  if (stats)
-    hipLaunchKernelGGL((as_dev::shared_kernel<W, SMAX, true, true>), dim3(grid), dim3(as_dev::kThreads),
-                       lds, s, a);
-  else if (usig)
-    hipLaunchKernelGGL((as_dev::shared_kernel<W, SMAX, true>), dim3(grid), dim3(as_dev::kThreads),
-                       lds, s, a);
-  else
-    hipLaunchKernelGGL((as_dev::shared_kernel<W, SMAX, false>), dim3(grid), dim3(as_dev::kThreads),
-                       lds, s, a);
-  return hipGetLastError();
+template <int SMAX>
+void lean_t(LeanKind kind, const KArgs& a, int jw, int64_t blocks, int waves, size_t lds, hipStream_t s) {
+  const dim3 grid((unsigned)blocks), block(64 * (unsigned)waves);
+  switch (kind) {
+    case LeanKind::kShared:
+      hipLaunchKernelGGL((as_dev::shared_kernel<AS_W, SMAX, false>), grid, block, lds, s, a, jw);
+      break;
+    case LeanKind::kStats:
+      hipLaunchKernelGGL((as_dev::shared_kernel<AS_W, SMAX, true>), grid, block, lds, s, a, jw);
+      break;
+    default: hipLaunchKernelGGL((as_dev::seg_kernel<AS_W, SMAX>), grid, block, lds, s, a); break;
+  }
 }
 
 }  // namespace
@@ -63,37 +61,18 @@ hipError_t launch_lds(int gpl, int smax, bool seg, const KArgs& a, size_t lds, h
 }
 
 template <int W>
-hipError_t launch_shared(int smax, bool usig, bool stats, const KArgs& a, size_t lds, hipStream_t s) {
+hipError_t launch_lean(LeanKind kind, int smax, const KArgs& a, int jw, int64_t blocks, int waves, size_t lds,
+                       hipStream_t s) {
   switch (smax) {
-    case 1: return shared_t<W, 1>(usig, stats, a, lds, s);
-    case 2: return shared_t<W, 2>(usig, stats, a, lds, s);
-    case 4: return shared_t<W, 4>(usig, stats, a, lds, s);
-    default: return shared_t<W, 8>(usig, stats, a, lds, s);
-  }
-}
-
-#if AS_W == 64
-hipError_t launch_seg64(int smax, const KArgs& a, int64_t blocks, size_t lds, hipStream_t s) {
-  const unsigned grid = (unsigned)blocks;
-  switch (smax) {
-    case 1:
-      hipLaunchKernelGGL((as_dev::seg_kernel<1>), dim3(grid), dim3(as_dev::kThreads), lds, s, a);
-      break;
-    case 2:
-      hipLaunchKernelGGL((as_dev::seg_kernel<2>), dim3(grid), dim3(as_dev::kThreads), lds, s, a);
-      break;
-    case 4:
-      hipLaunchKernelGGL((as_dev::seg_kernel<4>), dim3(grid), dim3(as_dev::kThreads), lds, s, a);
-      break;
-    default:
-      hipLaunchKernelGGL((as_dev::seg_kernel<8>), dim3(grid), dim3(as_dev::kThreads), lds, s, a);
-      break;
+    case 1: lean_t<1>(kind, a, jw, blocks, waves, lds, s); break;
+    case 2: lean_t<2>(kind, a, jw, blocks, waves, lds, s); break;
+    case 4: lean_t<4>(kind, a, jw, blocks, waves, lds, s); break;
+    default: lean_t<8>(kind, a, jw, blocks, waves, lds, s); break;
   }
   return hipGetLastError();
 }
-#endif
 
 template hipError_t launch_lds<AS_W>(int, int, bool, const KArgs&, size_t, hipStream_t);
-template hipError_t launch_shared<AS_W>(int, bool, bool, const KArgs&, size_t, hipStream_t);
+template hipError_t launch_lean<AS_W>(LeanKind, int, const KArgs&, int, int64_t, int, size_t, hipStream_t);
 
 }  // namespace as_host

@@ -11,22 +11,22 @@
 
 #include "sim_kernel.hpp"
 #include "sim_launch.hpp"
-#include "sim_shared.hpp"
+#include "sim_lean.hpp"
 
 namespace as_dev {
 namespace {
 
-template <bool USIG, bool STATS, int WL>
+template <bool STATS, int WL>
 __device__ __forceinline__ void multi_w(const KArgs& a, const JobSet& v, int64_t blk, int sl) {
   switch (sl) {
-    case 0: shared_body<1 << WL, 1, USIG, STATS, false>(a, v, blk); break;
-    case 1: shared_body<1 << WL, 2, USIG, STATS, false>(a, v, blk); break;
-    case 2: shared_body<1 << WL, 4, USIG, STATS, false>(a, v, blk); break;
-    default: shared_body<1 << WL, 8, USIG, STATS, false>(a, v, blk); break;
+    case 0: lean_body<1 << WL, 1, STATS, false>(a, v, blk); break;
+    case 1: lean_body<1 << WL, 2, STATS, false>(a, v, blk); break;
+    case 2: lean_body<1 << WL, 4, STATS, false>(a, v, blk); break;
+    default: lean_body<1 << WL, 8, STATS, false>(a, v, blk); break;
   }
 }
 
-template <bool USIG, bool STATS>
+template <bool STATS>
 __global__ __launch_bounds__(kThreads) void shared_multi(const KArgs* __restrict__ ap, const MultiSegs ms) {
   const KArgs& a = *ap;
   // this block's segment, with static indices only (the table stays in the
@@ -46,13 +46,13 @@ __global__ __launch_bounds__(kThreads) void shared_multi(const KArgs* __restrict
   }
   const int64_t blk = bx - b0;
   switch (wl) {
-    case 0: multi_w<USIG, STATS, 0>(a, v, blk, sl); break;
-    case 1: multi_w<USIG, STATS, 1>(a, v, blk, sl); break;
-    case 2: multi_w<USIG, STATS, 2>(a, v, blk, sl); break;
-    case 3: multi_w<USIG, STATS, 3>(a, v, blk, sl); break;
-    case 4: multi_w<USIG, STATS, 4>(a, v, blk, sl); break;
-    case 5: multi_w<USIG, STATS, 5>(a, v, blk, sl); break;
-    default: multi_w<USIG, STATS, 6>(a, v, blk, sl); break;
+    case 0: multi_w<STATS, 0>(a, v, blk, sl); break;
+    case 1: multi_w<STATS, 1>(a, v, blk, sl); break;
+    case 2: multi_w<STATS, 2>(a, v, blk, sl); break;
+    case 3: multi_w<STATS, 3>(a, v, blk, sl); break;
+    case 4: multi_w<STATS, 4>(a, v, blk, sl); break;
+    case 5: multi_w<STATS, 5>(a, v, blk, sl); break;
+    default: multi_w<STATS, 6>(a, v, blk, sl); break;
   }
 }
 
@@ -62,12 +62,12 @@ __global__ __launch_bounds__(kThreads) void shared_multi(const KArgs* __restrict
 namespace as_host {
 
 hipError_t launch_shared_multi(bool stats, const KArgs* a_dev, const as_dev::MultiSegs& ms, int64_t blocks,
-                               size_t lds, hipStream_t s) {
+                               int waves, size_t lds, hipStream_t s) {
   if (stats)
-    hipLaunchKernelGGL((as_dev::shared_multi<true, true>), dim3((unsigned)blocks), dim3(as_dev::kThreads), lds, s,
+    hipLaunchKernelGGL((as_dev::shared_multi<true>), dim3((unsigned)blocks), dim3(64 * (unsigned)waves), lds, s,
                        a_dev, ms);
   else
-    hipLaunchKernelGGL((as_dev::shared_multi<true, false>), dim3((unsigned)blocks), dim3(as_dev::kThreads), lds, s,
+    hipLaunchKernelGGL((as_dev::shared_multi<false>), dim3((unsigned)blocks), dim3(64 * (unsigned)waves), lds, s,
                        a_dev, ms);
   return hipGetLastError();
 }

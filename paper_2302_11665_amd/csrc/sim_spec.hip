@@ -923,10 +923,10 @@ __device__ __forceinline__ uint64_t round_chunk(SharedLane<SMAX>& st, const Shar
     uint32_t sr = 0;  // request e of the half at bit hc - 1 - e
     if (hc == 32) {
       for (int e = 0; e < 32; e += 4)
-        fast_batch<W, SMAX, 4, false, false, false, UNI>(st, c, sT + 2 * (h + e), sO + h + e, h + e, sr);
+        fast_batch<W, SMAX, 4, UNI>(st, c, sT + 2 * (h + e), sO + h + e, sr);
     } else {
       for (int e = 0; e < hc; ++e)
-        fast_batch<W, SMAX, 1, false, false, false, UNI>(st, c, sT + 2 * (h + e), sO + h + e, h + e, sr);
+        fast_batch<W, SMAX, 1, UNI>(st, c, sT + 2 * (h + e), sO + h + e, sr);
     }
     const uint32_t bits = hc == 32 ? __builtin_bitreverse32(sr) : (__builtin_bitreverse32(sr) >> (32 - hc));
     word |= (uint64_t)bits << h;
@@ -1042,17 +1042,10 @@ __global__ __launch_bounds__(64) void spec_round_fast(const SpecArgs a, int q) {
   c.lrow = sL + (cfg < 0 ? 0 : cfg) * SMAX;
   c.lshift = lshift;
   c.sigma = valid ? a.slo_scale[job % a.K] : 0.0;
-  c.fmask = 0;
-  c.frowp = nullptr;
-  c.flimit = 0;
-  c.fcnt = 0;
-  c.cnt = nullptr;
   SharedLane<SMAX> st;
 #pragma unroll
   for (int s = 0; s < SMAX; ++s) st.F[s] = (mine && ran) ? E_in[prv + (size_t)s * J] : 0.0;
-  st.fin_sum = st.hash = st.served = 0;  // served: the job's count, in every lane of it
-  st.wlo = 0;
-  st.busy = 0.0;
+  st.fin_sum = st.served = 0;  // served: the job's count, in every lane of it
   __syncthreads();
 
   const int64_t b = seg_bound(a.n, a.nseg, k), e = seg_bound(a.n, a.nseg, k + 1);
