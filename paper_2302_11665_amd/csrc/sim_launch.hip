@@ -4,6 +4,7 @@
 #include "sim_kernel.hpp"
 #include "sim_launch.hpp"
 #include "sim_lean.hpp"
+#include "sim_spec.hpp"
 
 #ifndef AS_W
 #error "compile with -DAS_W=<lanes per job>"
@@ -71,6 +72,21 @@ hipError_t launch_lean(LeanKind kind, int smax, const KArgs& a, int jw, int64_t 
   }
   return hipGetLastError();
 }
+
+#if AS_W >= 4
+template <int W>
+hipError_t launch_fix(int smax, const as_dev::SpecArgs& a, int q, int64_t blocks, size_t lds, hipStream_t s) {
+  const dim3 grid((unsigned)blocks), block(64);
+  switch (smax) {
+    case 1: hipLaunchKernelGGL((as_dev::spec_fix<W, 1>), grid, block, lds, s, a, q); break;
+    case 2: hipLaunchKernelGGL((as_dev::spec_fix<W, 2>), grid, block, lds, s, a, q); break;
+    case 4: hipLaunchKernelGGL((as_dev::spec_fix<W, 4>), grid, block, lds, s, a, q); break;
+    default: hipLaunchKernelGGL((as_dev::spec_fix<W, 8>), grid, block, lds, s, a, q); break;
+  }
+  return hipGetLastError();
+}
+template hipError_t launch_fix<AS_W>(int, const as_dev::SpecArgs&, int, int64_t, size_t, hipStream_t);
+#endif
 
 template hipError_t launch_lds<AS_W>(int, int, bool, const KArgs&, size_t, hipStream_t);
 template hipError_t launch_lean<AS_W>(LeanKind, int, const KArgs&, int, int64_t, int, size_t, hipStream_t);

@@ -7,6 +7,10 @@
 #include "sim_kernel.hpp"
 #include "sim_shared.hpp"
 
+namespace as_dev {
+struct SpecArgs;
+}
+
 namespace as_host {
 
 using as_dev::KArgs;
@@ -29,6 +33,18 @@ hipError_t launch_lean(LeanKind kind, int smax, const KArgs& a, int jw, int64_t 
 // common arguments in device memory, unchanged until the launch has run.
 hipError_t launch_shared_multi(bool stats, const KArgs* a_dev, const as_dev::MultiSegs& ms, int64_t blocks,
                                int waves, size_t lds, hipStream_t s);
+
+// Round q of the speculative kernels' fix-ups (sim_spec.hpp), one job per
+// wavefront, W = 4 .. 64 lanes hold the groups.
+template <int W>
+hipError_t launch_fix(int smax, const as_dev::SpecArgs& a, int q, int64_t blocks, size_t lds, hipStream_t s);
+extern template hipError_t launch_fix<4>(int, const as_dev::SpecArgs&, int, int64_t, size_t, hipStream_t);
+extern template hipError_t launch_fix<8>(int, const as_dev::SpecArgs&, int, int64_t, size_t, hipStream_t);
+extern template hipError_t launch_fix<16>(int, const as_dev::SpecArgs&, int, int64_t, size_t, hipStream_t);
+extern template hipError_t launch_fix<32>(int, const as_dev::SpecArgs&, int, int64_t, size_t, hipStream_t);
+extern template hipError_t launch_fix<64>(int, const as_dev::SpecArgs&, int, int64_t, size_t, hipStream_t);
+// The same for any group count; the grid and the LDS are chosen here.
+hipError_t launch_fix_any(int smax, const as_dev::SpecArgs& a, int q, hipStream_t s);
 
 #define AS_DECLARE_W(W)                                                                       \
   extern template hipError_t launch_lds<W>(int, int, bool, const KArgs&, size_t, hipStream_t); \

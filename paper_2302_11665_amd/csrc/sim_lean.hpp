@@ -275,28 +275,123 @@ struct LeanOut {
   double busy;  // this lane's group's
 };
 
-// sL: stage-latency table [M][Cp][SMAX] in LDS, a model's rows 1 << lshift
-// bytes apart; rec: lean_wave_bytes of LDS of this wavefront (16-byte
-// aligned); cnt: STATS, this wavefront's [jw][M] served counters, zeroed.
-// Called by whole wavefronts in uniform control flow (the commit restores a
-// full exec mask).
+// What a wavefront keeps for all its chunks.
+template <int W, int SMAX>
+struct LeanWave {
+  const char* lrow;  // this lane's configuration's latency row of model 0 (LDS)
+  const char* urow;  // the first group's (UNI: every group's)
+  int lshift;        // a model's rows are 1 << lshift bytes apart
+  unsigned char* rec;  // lean_wave_bytes of LDS, then finish times by rank (ROW)
+  double slo;          // lane m: model m's SLO
+  uint64_t hm;         // lane m: lanes whose group hosts model m
+  uint64_t hosted;     // models some job hosts
+  uint32_t blo, bhi;   // this lane's job's lanes below it
+};
+
+// sL: stage-latency table [M][Cp][SMAX] in LDS; cfg: this lane's group's
+// configuration, -1: no group.
+template <int W, int SMAX, class Args>
+__device__ __forceinline__ LeanWave<W, SMAX> lean_wave(const Args& a, double sigma, int cfg, uint64_t hm,
+                                                       const double* sL, int lshift, unsigned char* rec) {
+  LeanWave<W, SMAX> w;
+  const int lane = threadIdx.x & 63;
+  const uint64_t valid = __builtin_amdgcn_ballot_w64(cfg >= 0);
+  const int c = cfg < 0 ? 0 : cfg;
+  w.lrow = reinterpret_cast<const char*>(sL + c * SMAX);
+  w.urow = reinterpret_cast<const char*>(
+      sL + (valid ? __builtin_amdgcn_readlane(c, __builtin_ctzll(valid)) : 0) * SMAX);
+  w.lshift = lshift;
+  w.rec = rec;
+  w.slo = lane < a.M ? sigma * a.d_single[lane] : 0.0;
+  w.hm = hm;
+  w.hosted = __builtin_amdgcn_ballot_w64(hm != 0);
+  const uint64_t below = ((1ull << lane) - 1) & ~((1ull << (lane / W * W)) - 1);
+  w.blo = (uint32_t)below;
+  w.bhi = (uint32_t)(below >> 32);
+  return w;
+}
+
+// One configuration for every group of the wavefront?
+__device__ __forceinline__ bool lean_uni(int cfg) {
+  const uint64_t valid = __builtin_amdgcn_ballot_w64(cfg >= 0);
+  const int cfg0 = valid ? __builtin_amdgcn_readlane(cfg, __builtin_ctzll(valid)) : 0;
+  return __builtin_amdgcn_ballot_w64(cfg >= 0 && cfg != cfg0) == 0;
+}
+
+// One chunk: lane e holds request e (mine: it exists and some job hosts it;
+// rank: hosted requests before it).  Returns the job's accept bits in all its
+// lanes, the request of rank k at bit k.  ROW: finish times (-1: rejected) by
+// rank are left behind the staged requests.  Called by whole wavefronts in
+// uniform control flow (the commit restores a full exec mask).
+template <int W, int SMAX, bool UNI, bool STATS, bool ROW>
+__device__ __forceinline__ uint64_t lean_chunk(LeanLane<SMAX>& st, const LeanWave<W, SMAX>& w, double tv, int mv,
+                                               bool mine, int rank, int nh) {
+  constexpr int R = lean_stride(SMAX);
+  if (nh == 0) return 0;
+  const int lane = threadIdx.x & 63;
+  uint64_t word = 0;  // this lane's accept bits
+  double* orow = reinterpret_cast<double*>(w.rec + (64 + kLeanB) * R);
+  const uint32_t olds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) double*)orow;
+  // stage the hosted requests, then requests that no lane hosts up to a
+  // whole batch
+  const int from = (mv & 63) << 2;
+  const double ms = __hiloint2double(__builtin_amdgcn_ds_bpermute(from, __double2hiint(w.slo)),
+                                     __builtin_amdgcn_ds_bpermute(from, __double2loint(w.slo)));
+  const uint32_t hl = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)w.hm);
+  const uint32_t hh = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)(w.hm >> 32));
+  lean_fence();
+  if (mine) {
+    unsigned char* r = w.rec + rank * R;
+    *(double2*)r = make_double2(tv, tv + ms);  // the deadline t + SLO, each rounded once
+    const uint32_t off = (uint32_t)mv << w.lshift;
+    if constexpr (UNI) {
+      const double* l = reinterpret_cast<const double*>(w.urow + off);
+      ulonglong2 h;
+      h.x = ((uint64_t)hh << 32) | hl;
+      h.y = (uint64_t)__double_as_longlong(l[0]);
+      *(ulonglong2*)(r + 16) = h;
+#pragma unroll
+      for (int s = 1; s < SMAX; ++s) *(double*)(r + 24 + 8 * s) = l[s];
+    } else {
+      *(uint4*)(r + 16) = make_uint4(hl, hh, off, 0u);
+    }
+  }
+  if (lane < kLeanB) {
+    unsigned char* r = w.rec + (nh + lane) * R;
+    *(double2*)r = make_double2(0.0, 0.0);
+    *(uint4*)(r + 16) = make_uint4(0u, 0u, 0u, 0u);
+  }
+  if constexpr (ROW) {
+    orow[lane] = -1.0;
+    if (lane < kLeanB) orow[64 + lane] = -1.0;
+  }
+  lean_fence();
+  const int nb = (nh + kLeanB - 1) / kLeanB;
+  for (int b = 0; b < nb; ++b) {
+    const uint32_t bits = lean_batch<W, SMAX, UNI, STATS, ROW>(st, w.rec + b * kLeanB * R, w.lrow, w.blo, w.bhi,
+                                                               olds + b * kLeanB * 8);
+    word |= (uint64_t)bits << (b * kLeanB);
+  }
+  return seg_or<W>(word);
+}
+
+// Whether the request in this lane is one to simulate, how many there are
+// (nh) and how many come before it (rank).
+template <int W, int SMAX>
+__device__ __forceinline__ bool lean_mine(const LeanWave<W, SMAX>& w, bool in, int mv, int& rank, int& nh) {
+  const bool mine = in && (unsigned)mv < 64u && ((w.hosted >> (mv & 63)) & 1u);
+  const uint64_t todo = __builtin_amdgcn_ballot_w64(mine);
+  nh = (int)__builtin_popcountll(todo);
+  rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(todo >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)todo, 0u));
+  return mine;
+}
+
+// cnt: STATS, this wavefront's [jw][M] served counters in LDS, zeroed.
 template <int W, int SMAX, bool UNI, bool STATS, bool ROW>
 __device__ __forceinline__ LeanOut lean_run(const KArgs& a, const LeanIn& in, const double* sL, int lshift,
                                             unsigned char* rec, uint32_t* cnt) {
-  constexpr int JW = 64 / W;
-  constexpr int R = lean_stride(SMAX);
   const int lane = threadIdx.x & 63;
-  const int cfg = in.cfg < 0 ? 0 : in.cfg;
-  const char* lrow = reinterpret_cast<const char*>(sL + cfg * SMAX);
-  const uint64_t valid = __builtin_amdgcn_ballot_w64(in.cfg >= 0);
-  const int cfg0 = valid ? __builtin_amdgcn_readlane(cfg, __builtin_ctzll(valid)) : 0;
-  const char* urow = reinterpret_cast<const char*>(sL + cfg0 * SMAX);  // UNI: every group's rows
-  const double slo = lane < a.M ? in.sigma * a.d_single[lane] : 0.0;  // lane m: model m's SLO
-  const uint64_t hosted = __builtin_amdgcn_ballot_w64(in.hm != 0);
-  // this lane's job's lanes below it
-  const uint64_t below = ((1ull << lane) - 1) & ~((1ull << (lane / W * W)) - 1);
-  const uint32_t blo = (uint32_t)below, bhi = (uint32_t)(below >> 32);
-
+  const LeanWave<W, SMAX> w = lean_wave<W, SMAX>(a, in.sigma, in.cfg, in.hm, sL, lshift, rec);
   LeanLane<SMAX> st;
 #pragma unroll
   for (int s = 0; s < SMAX; ++s) st.F[s] = 0.0;
@@ -315,58 +410,9 @@ __device__ __forceinline__ LeanOut lean_run(const KArgs& a, const LeanIn& in, co
     const int64_t ahead = base + 64 + lane;
     tn = in.t[ahead < n ? ahead : top];
     mn = in.model[ahead < n ? ahead : top];
-    const bool mine = base + lane < n && (unsigned)mv < 64u && ((hosted >> (mv & 63)) & 1u);
-    const uint64_t todo = __builtin_amdgcn_ballot_w64(mine);
-    const int nh = (int)__builtin_popcountll(todo);
-    const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(todo >> 32),
-                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)todo, 0u));
-    uint64_t word = 0;  // this lane's accept bits, staged request k at bit k
-    double* orow = reinterpret_cast<double*>(rec + (64 + kLeanB) * R);  // ROW: finish times by rank
-    const uint32_t olds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) double*)orow;
-    if (nh > 0) {
-      // stage the hosted requests, then requests that no lane hosts up to a
-      // whole batch
-      const int from = (mv & 63) << 2;
-      const double ms = __hiloint2double(__builtin_amdgcn_ds_bpermute(from, __double2hiint(slo)),
-                                         __builtin_amdgcn_ds_bpermute(from, __double2loint(slo)));
-      const uint32_t hl = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)in.hm);
-      const uint32_t hh = W * JW <= 32 ? 0u : (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)(in.hm >> 32));
-      lean_fence();
-      if (mine) {
-        unsigned char* r = rec + rank * R;
-        *(double2*)r = make_double2(tv, tv + ms);  // the deadline t + SLO, each rounded once
-        const uint32_t off = (uint32_t)mv << lshift;
-        if constexpr (UNI) {
-          const double* l = reinterpret_cast<const double*>(urow + off);
-          ulonglong2 h;
-          h.x = ((uint64_t)hh << 32) | hl;
-          h.y = (uint64_t)__double_as_longlong(l[0]);
-          *(ulonglong2*)(r + 16) = h;
-#pragma unroll
-          for (int s = 1; s < SMAX; ++s) *(double*)(r + 24 + 8 * s) = l[s];
-        } else {
-          *(uint4*)(r + 16) = make_uint4(hl, hh, off, 0u);
-        }
-      }
-      if (lane < kLeanB) {
-        unsigned char* r = rec + (nh + lane) * R;
-        *(double2*)r = make_double2(0.0, 0.0);
-        *(uint4*)(r + 16) = make_uint4(0u, 0u, 0u, 0u);
-      }
-      if constexpr (ROW) {
-        orow[lane] = -1.0;
-        if (lane < kLeanB) orow[64 + lane] = -1.0;
-      }
-      lean_fence();
-      const int nb = (nh + kLeanB - 1) / kLeanB;
-      for (int b = 0; b < nb; ++b) {
-        const uint32_t bits =
-            lean_batch<W, SMAX, UNI, STATS, ROW>(st, rec + b * kLeanB * R, lrow, blo, bhi, olds + b * kLeanB * 8);
-        word |= (uint64_t)bits << (b * kLeanB);
-      }
-    }
-    // the job's accept bits, in all its lanes
-    word = seg_or<W>(word);
+    int rank, nh;
+    const bool mine = lean_mine<W, SMAX>(w, base + lane < n, mv, rank, nh);
+    uint64_t word = lean_chunk<W, SMAX, UNI, STATS, ROW>(st, w, tv, mv, mine, rank, nh);
     served += __builtin_popcountll(word);
     if (STATS || (in.digest && nh < 64)) {
       // back to trace order: lane e is request e, whose bit is at its rank
@@ -387,6 +433,7 @@ __device__ __forceinline__ LeanOut lean_run(const KArgs& a, const LeanIn& in, co
     if (in.digest) hash = (hash ^ word) * kHashMul;
     if constexpr (ROW) {
       lean_fence();
+      const double* orow = reinterpret_cast<const double*>(rec + (64 + kLeanB) * lean_stride(SMAX));
       if (base + lane < in.row_n) in.row[base + lane] = mine ? orow[rank] : -2.0;
     }
   }
@@ -404,8 +451,8 @@ __host__ __device__ constexpr size_t lean_lds_bytes(int W, int M, int Cp, int SM
 
 // The stage-latency table padded with zero-latency stages (sim_kernel.hpp);
 // returns log2 of a model's row stride in bytes and the table's bytes.
-template <int SMAX>
-__device__ __forceinline__ int lean_table(const KArgs& a, double* sL, size_t& bytes) {
+template <int SMAX, class Args>
+__device__ __forceinline__ int lean_table(const Args& a, double* sL, size_t& bytes) {
   int cp = 1, lshift = 0;
   while (cp < a.C) cp <<= 1;
   while ((1 << lshift) < cp * SMAX * 8) ++lshift;
@@ -422,10 +469,7 @@ __device__ __forceinline__ int lean_table(const KArgs& a, double* sL, size_t& by
 template <int W, int SMAX, bool STATS, bool ROW>
 __device__ __forceinline__ LeanOut lean_go(const KArgs& a, const LeanIn& in, const double* sL, int lshift,
                                            unsigned char* rec, uint32_t* cnt) {
-  // one configuration for every group of the wavefront?
-  const uint64_t valid = __builtin_amdgcn_ballot_w64(in.cfg >= 0);
-  const int cfg0 = valid ? __builtin_amdgcn_readlane(in.cfg, __builtin_ctzll(valid)) : 0;
-  if (__builtin_amdgcn_ballot_w64(in.cfg >= 0 && in.cfg != cfg0) == 0)
+  if (lean_uni(in.cfg))
     return lean_run<W, SMAX, true, STATS, ROW>(a, in, sL, lshift, rec, cnt);
   return lean_run<W, SMAX, false, STATS, ROW>(a, in, sL, lshift, rec, cnt);
 }

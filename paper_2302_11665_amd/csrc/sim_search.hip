@@ -188,6 +188,11 @@ int beam_search(const as_trace_t* trace, const as_models_t* models, const int64_
   a.n = trace->n;
   a.slo_scale = static_cast<const double*>(d.p[1]);
   a.K = 1;
+  // A search's late selections saturate groups, and runs from different states
+  // then do not meet: its steps are cut only into segments this long (151,513
+  // requests on the speculative kernels, every step's shapes launched apart,
+  // took three times as long as on the others).
+  a.min_segment = 131072;
   // kernel shape of each search: lanes per job (its group count rounded up
   // to a power of two) and padded stage count (its deepest configuration)
   std::vector<int> shape_of(R), shape_w, shape_s;

@@ -13,28 +13,22 @@
 //            the requests just before the segment from the empty state
 //            (all F = 0), then runs the segment from that estimate,
 //            recording its results and the state at its end;
-//   round q  segment k whose recorded start state differs from the end state
-//            segment k-1 now has re-runs its requests from that end state
-//            until its state equals, bit for bit, the state its current
-//            results had at the same request (pass 0 saves the state every
-//            few thousand requests): from there on both runs take identical
-//            decisions (the state is the only thing a request depends on
-//            besides its own arrival), so the old results stand and only the
-//            re-run prefix is replaced.  A segment whose runs never meet gets
-//            a new end state, and its successor is revisited next round.
-//            A round re-runs few jobs and lasts as long as the longest
-//            re-run, so for jobs of at most 16 groups it runs in a
-//            group-per-lane layout (a job's groups on W lanes, state in
-//            registers, DPP min dispatch), whose per-request chain is shorter.
+//   fix-ups  a segment whose recorded start state is not its predecessor's end
+//            state is simulated again from there until its state equals, bit
+//            for bit, the state its current results had at the same request
+//            (pass 0 saves the state every few thousand requests): from there
+//            on both runs take identical decisions (the state is the only
+//            thing a request depends on besides its own arrival), so the old
+//            results stand and only the re-run prefix is replaced.  All such
+//            segments at once in a few rounds, then job by job (sim_spec.hpp);
 //   final    per job: served counts and finish-time sums add up over
 //            segments; the digest's ordered hash runs over the accept bitmap.
 //
 // After round q segments 0..q hold exact results (segment 0 starts from the
-// true empty state; each round settles at least the next one), so nseg - 1
-// rounds always suffice; a round whose predecessor changed nothing returns at
-// once.  Bursty arrivals make the speculation cheap: two runs of one job from
-// different states become identical within a few thousand requests, so the
-// warm-up estimate is usually exact and the rounds re-run little.
+// true empty state), so nseg - 1 rounds always suffice; a round with nothing
+// listed returns at once.  Bursty arrivals make the speculation cheap: two runs
+// of one job from different states become identical within a few thousand
+// requests, so the warm-up estimate is usually exact and little is redone.
 //
 // State layout: F[g][s] of a lane lives in LDS as [g][s][lane] (conflict-free
 // for any per-lane g), with a spare row that unserved requests write and a
@@ -56,81 +50,17 @@
 #include "alpaserve_sim.h"
 #include "sim_internal.hpp"
 #include "sim_kernel.hpp"
-#include "sim_shared.hpp"
+#include "sim_launch.hpp"
+#include "sim_spec.hpp"
 
 namespace as_dev {
 namespace {
 
-constexpr int kSpecMaxSeg = 64;
-// A reconciliation re-run that has not met the old results after this many
-// requests gives up, and the call falls back to the shared-trace kernels.  On
-// bursty traffic runs from different states meet within a few thousand
-// requests (on the 8192-placement heavy trace a cap of 32,768 gives up and one
-// of 65,536 does not); where groups stay saturated they may never meet, and
-// every round would then re-run whole segments (that heavy trace with each
-// model kept on two groups: 2.29 s per call without the cap, 0.92 s with it,
-// 0.56 s on the shared-trace kernel alone).
-constexpr int64_t kSpecGiveUp = 131072;
 // Jobs per wavefront: one lane per job.  (32 jobs per wavefront halves the
 // state, so a SIMD holds two wavefronts; on the 8192-placement workload that
 // took 305 ms against 276: the two did not overlap enough to pay for doubling
 // the instructions per job.)
 constexpr int kSpecJobsPerWave = 64;
-constexpr uint64_t kSpecHashMul = 0x9E3779B97F4A7C15ULL;
-
-struct SpecArgs {
-  const double* t;
-  const int32_t* model;
-  int64_t n;
-  const double* d_single;
-  const double* stage_lat;
-  const int32_t* group_cfg;
-  const uint64_t* host_mask;
-  const double* slo_scale;
-  int64_t* out_served;
-  double* out_attain;
-  uint64_t* out_digest;
-  double* out_finish;
-  // workspace
-  uint64_t* bitmap;     // [nw][J] accept bits, 64 requests per word
-  double* st_start;     // [nseg][G*SMAX][J] start state behind each segment's results
-  double* st_end;       // [2][nseg][G*SMAX][J] end states, alternating between rounds
-  int64_t* seg_served;  // [nseg][J]
-  uint64_t* seg_fsum;   // [nseg][J]
-  double* ckpt;         // [nseg][ckps][G*SMAX][J] states every ck requests into a segment
-  int64_t* ck_served;   // [nseg][ckps][J] served count of the segment before each checkpoint
-  uint64_t* ck_fsum;    // [nseg][ckps][J] finish-time sum likewise
-  int64_t ck;           // checkpoint interval (a multiple of 64)
-  int32_t ckps;         // checkpoints per segment (upper bound)
-  int32_t* changed;     // [nseg] segments whose end state changed, per round
-  int32_t* cfg_info;    // [3]: 1 when every used group has one configuration; that configuration;
-                        // 1 once a re-run gave up (the results are then left to other kernels)
-  int64_t cap;          // requests a re-run may take without meeting the old results before giving up
-  int64_t nw;
-  int64_t warmup;  // requests simulated before a segment to estimate its start state
-  int32_t M, C, smax_in, G, K, J, n_finish, nseg, njb;
-  int32_t cfg_stages[AS_MAX_CONFIGS];
-  int32_t finish_jobs[AS_MAX_FINISH];
-};
-
-__host__ __device__ constexpr int pow2ceil_dev(int x) {
-  int p = 1;
-  while (p < x) p <<= 1;
-  return p;
-}
-
-// Rounds in the group-per-lane layout where it applies; ALPASERVE_SPEC_ROUNDS=lane
-// keeps the one-lane-per-job round kernel (tests cover both).
-inline bool spec_gpl_rounds() {
-  const char* e = getenv("ALPASERVE_SPEC_ROUNDS");
-  return !(e && std::strcmp(e, "lane") == 0);
-}
-
-__device__ __forceinline__ int64_t seg_bound(int64_t n, int nseg, int k) {
-  return k >= nseg ? n : ((n * k / nseg) & ~(int64_t)63);
-}
-
-__device__ __forceinline__ uint64_t bits_of(double x) { return (uint64_t)__double_as_longlong(x); }
 
 // Accept bits of a chunk: each request's bit enters at the top and moves down
 // one place per request, so that after the chunk's cnt requests chunk_word
@@ -575,7 +505,6 @@ __device__ __forceinline__ void spec_range(const SpecArgs& a, const SpecLds<SMAX
   }
 }
 
-__device__ __forceinline__ int spec_ckpts(int64_t b, int64_t e, int64_t ck) { return (int)((e - b - 1) / ck); }
 
 // Pass 0 of one wavefront (the per-request output rows are written by
 // spec_rows once the rounds have made every saved state exact).
@@ -588,7 +517,7 @@ __device__ __forceinline__ void spec_pass0_body(const SpecArgs& a, double* lds, 
   const int GS = a.G * SMAX;
   if (lane < JPW)
     for (int q = 0; q < GS; ++q) s.F[q * JPW + lane] = 0.0;
-  if (blockIdx.x == 0 && lane < a.nseg) a.changed[lane] = lane == 0 ? 1 : 0;
+  if (k == 0 && ln.valid) a.claimed[ln.job] = 0;
 
   const int64_t b = seg_bound(a.n, a.nseg, k), e = seg_bound(a.n, a.nseg, k + 1);
   const int64_t J = a.J;
@@ -644,7 +573,7 @@ __device__ __forceinline__ void spec_pass0_body(const SpecArgs& a, double* lds, 
     fsum = 0;
   }
   if (!ln.valid) return;
-  for (int q = 0; q < GS; ++q) a.st_end[seg_base + (size_t)q * J] = s.F[q * JPW + lane];  // buffer 0
+  for (int q = 0; q < GS; ++q) a.st_end[seg_base + (size_t)q * J] = a.xch[0][seg_base + (size_t)q * J] = s.F[q * JPW + lane];
   a.seg_served[(size_t)k * J + ln.job] = served;
   a.seg_fsum[(size_t)k * J + ln.job] = fsum;
 }
@@ -786,359 +715,17 @@ __global__ __launch_bounds__(64) void spec_rows(const SpecArgs a, int nfb) {
     rows_body<SMAX, MB, UCFG, JPW, false>(a, lds, lane, ln, c0, k, pc, pb, pe);
 }
 
-// Round q >= 1: a segment whose start state differs from its predecessor's
-// end state re-runs from that end state, comparing its state with the saved
-// checkpoints of its current results: where they are equal the two runs
-// coincide from there on, so the re-run stops and only its prefix replaces
-// the old results.  Checkpoints passed before that point are replaced with
-// the new run's.
-template <int SMAX, int MB, bool UCFG, int JPW, bool EXTRA>
-__global__ __launch_bounds__(64) void spec_round(const SpecArgs a, int q) {
-  if ((a.cfg_info[0] != 0) != UCFG) return;
-  if (a.cfg_info[2] != 0) return;     // a re-run gave up: other kernels take over
-  if (a.changed[q - 1] == 0) return;  // nothing moved in the previous round: done
-  const int c0 = UCFG ? a.cfg_info[1] : 0;
-  extern __shared__ double lds[];
-  const int lane = threadIdx.x;
-  const int jb = blockIdx.x % a.njb;
-  const int k = blockIdx.x / a.njb;
-  const SpecLane ln = spec_lane<JPW>(a, jb, lane);
-  const int GS = a.G * SMAX;
-  const int64_t J = a.J;
-  const size_t per_buf = (size_t)a.nseg * GS * J;
-  const double* E_in = a.st_end + (size_t)((q - 1) & 1) * per_buf;
-  double* E_out = a.st_end + (size_t)(q & 1) * per_buf;
-  const size_t own = ((size_t)k * GS) * J + ln.job;
-  const size_t prv = k > 0 ? ((size_t)(k - 1) * GS) * J + ln.job : 0;
-  LaneMasks<MB> msk;
-  const bool many = msk.load(a.host_mask + (int64_t)ln.p * a.M, a.M, a.G, ln.valid);
-  if ((__builtin_amdgcn_ballot_w64(many) != 0) != EXTRA) return;
-
-  bool active = false;
-  if (ln.valid && k > 0)
-    for (int x = 0; x < GS; ++x)
-      active |= bits_of(a.st_start[own + (size_t)x * J]) != bits_of(E_in[prv + (size_t)x * J]);
-  const bool ran = active;
-  if (__builtin_amdgcn_ballot_w64(active) == 0) {
-    if (ln.valid)
-      for (int x = 0; x < GS; ++x) E_out[own + (size_t)x * J] = E_in[own + (size_t)x * J];
-    return;
-  }
-  const auto s = spec_tables<SMAX, UCFG, JPW>(a, lds, lane, ln.p, ln.valid, c0);
-  if (lane < JPW)
-    for (int x = 0; x < GS; ++x) s.F[x * JPW + lane] = active ? E_in[prv + (size_t)x * J] : 0.0;
-
-  const int64_t b = seg_bound(a.n, a.nseg, k), e = seg_bound(a.n, a.nseg, k + 1);
-  const size_t ck0 = (size_t)k * a.ckps;
-  const int nck = b < e ? spec_ckpts(b, e, a.ck) : 0;
-  int64_t served = 0;
-  uint64_t fsum = 0, word = 0;
-  bool coupled = false, gave_up = false;
-  spec_range<SMAX, MB, UCFG, JPW, EXTRA, false>(
-      a, s, msk, ln, lane, b, e, active,
-      [&](int64_t cb) {
-        if (cb > b && (cb - b) % a.ck == 0 && active) {
-          const int jl = (int)((cb - b) / a.ck) - 1;
-          const size_t j = ck0 + (size_t)jl;
-          bool same = true;
-          for (int x = 0; x < GS; ++x)
-            same &= bits_of(a.ckpt[(j * GS + x) * J + ln.job]) == bits_of(s.F[x * JPW + lane]);
-          const int64_t old_s = a.ck_served[j * J + ln.job];
-          const uint64_t old_f = a.ck_fsum[j * J + ln.job];
-          if (same) {
-            // the old results stand from here on; later checkpoints' running
-            // totals shift by the prefix's change
-            coupled = true;
-            active = false;
-            const int64_t ds = served - old_s;
-            const uint64_t df = fsum - old_f;
-            a.seg_served[(size_t)k * J + ln.job] += ds;
-            a.seg_fsum[(size_t)k * J + ln.job] += df;
-            a.ck_served[j * J + ln.job] = served;
-            a.ck_fsum[j * J + ln.job] = fsum;
-            for (int j2 = jl + 1; j2 < nck; ++j2) {
-              a.ck_served[(ck0 + j2) * J + ln.job] += ds;
-              a.ck_fsum[(ck0 + j2) * J + ln.job] += df;
-            }
-          } else {
-            for (int x = 0; x < GS; ++x) a.ckpt[(j * GS + x) * J + ln.job] = s.F[x * JPW + lane];
-            a.ck_served[j * J + ln.job] = served;
-            a.ck_fsum[j * J + ln.job] = fsum;
-          }
-        }
-        const bool any = __builtin_amdgcn_ballot_w64(active) != 0;
-        if (any && cb - b >= a.cap) {
-          // runs from the two states do not meet: the pipeline gives up
-          if (lane == 0) a.cfg_info[2] = 1;
-          gave_up = true;
-          return 0;
-        }
-        return any ? 1 : 0;
-      },
-      [&](int64_t i, int r, double out, bool sv, bool rows) {
-        (void)i;
-        (void)r;
-        (void)rows;
-        fsum += sv ? bits_of(out) : 0;
-        word = push_bit(word, sv);
-      },
-      [&](int64_t cb, int cnt) {
-        word = chunk_word(word, cnt);
-        if (active) a.bitmap[(cb >> 6) * J + ln.job] = word;
-        served += __popcll(word);
-        word = 0;
-      });
-
-  if (gave_up || !ln.valid) return;
-  if (ran) {
-    // the predecessor's end state now stands behind this segment's results
-    for (int x = 0; x < GS; ++x) a.st_start[own + (size_t)x * J] = E_in[prv + (size_t)x * J];
-    if (!coupled) {
-      // re-run to the end: its totals replace the old ones, and unless it
-      // ends in the old end state its successor must be revisited
-      a.seg_served[(size_t)k * J + ln.job] = served;
-      a.seg_fsum[(size_t)k * J + ln.job] = fsum;
-      bool same = true;
-      for (int x = 0; x < GS; ++x) same &= bits_of(E_in[own + (size_t)x * J]) == bits_of(s.F[x * JPW + lane]);
-      if (!same) {
-        for (int x = 0; x < GS; ++x) E_out[own + (size_t)x * J] = s.F[x * JPW + lane];
-        atomicAdd(a.changed + q, 1);
-        return;
-      }
-    }
-  }
-  for (int x = 0; x < GS; ++x) E_out[own + (size_t)x * J] = E_in[own + (size_t)x * J];
-}
-
-// One 64-request chunk (cnt <= 64 of them, staged in LDS) of a round in the
-// group-per-lane layout, run by the shared-trace kernel's request step;
-// returns the job's accept word (request r at bit r, in every lane of the
-// job) and adds its population count to the job's served count.
-template <int W, int SMAX, bool UNI>
-__device__ __forceinline__ uint64_t round_chunk(SharedLane<SMAX>& st, const SharedConst& c, const double* sT,
-                                                const uint32_t* sO, int cnt) {
-  uint64_t word = 0;
-  for (int h = 0; h < cnt; h += 32) {
-    const int hc = (cnt - h) < 32 ? (cnt - h) : 32;
-    uint32_t sr = 0;  // request e of the half at bit hc - 1 - e
-    if (hc == 32) {
-      for (int e = 0; e < 32; e += 4)
-        fast_batch<W, SMAX, 4, UNI>(st, c, sT + 2 * (h + e), sO + h + e, sr);
-    } else {
-      for (int e = 0; e < hc; ++e)
-        fast_batch<W, SMAX, 1, UNI>(st, c, sT + 2 * (h + e), sO + h + e, sr);
-    }
-    const uint32_t bits = hc == 32 ? __builtin_bitreverse32(sr) : (__builtin_bitreverse32(sr) >> (32 - hc));
-    word |= (uint64_t)bits << h;
-  }
-  const uint64_t wj = seg_or<W>(word);
-  st.served += (uint64_t)__popcll(wj);
-  return wj;
-}
-
-// LDS bytes of spec_round_fast: M + 1 model records (the last hosts nothing
-// and stands for an out-of-range model id), the stage-latency table
-// [M][Cp][SMAX] and one staged chunk (arrivals at stride 2, record offsets).
-__host__ __device__ constexpr size_t round_fast_lds_bytes(int M, int Cp, int SMAX) {
-  return (size_t)(M + 1) * ((size_t)1 << rec_shift(SMAX)) + (size_t)M * Cp * SMAX * 8 + 128 * 8 + 64 * 4;
-}
-
-// Round q >= 1 in the group-per-lane layout (jobs of at most 16 groups): the
-// protocol of spec_round with a job's groups on W lanes, their stage free
-// times in registers, and the shared-trace kernel's request step --
-// per-wavefront model records in LDS (hosting lanes, the count that says
-// whether a dispatch minimum is needed, stage latencies, d_single), the
-// two-level integer minimum, four requests' inputs read together.  A round
-// re-runs few jobs and lasts as long as its longest re-run, and per request
-// this layout is a shorter chain than one lane per job.  Stages past a
-// group's depth have zero latency, as in the other speculative kernels, so
-// saved states compare bit for bit.  Only the jobs that re-run host models in
-// the records; a job that has met the old results keeps simulating with the
-// others but writes nothing more.  Each 64-request chunk is staged in LDS
-// from registers loaded a chunk ahead.
-template <int W, int SMAX>
-__global__ __launch_bounds__(64) void spec_round_fast(const SpecArgs a, int q) {
-  constexpr int JW = 64 / W;  // jobs per wavefront
-  constexpr int RSH = rec_shift(SMAX);
-  if (a.cfg_info[2] != 0) return;  // a re-run gave up: other kernels take over
-  if (a.changed[q - 1] == 0) return;
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int lane = threadIdx.x;
-  const int g = lane % W, slot = lane / W;
-  const int njbw = (a.J + JW - 1) / JW;
-  const int k = blockIdx.x / njbw, jb = blockIdx.x % njbw;
-  const int job = jb * JW + slot;
-  const bool valid = job < a.J;
-  const bool mine = valid && g < a.G;  // this lane holds a group of a job
-  const int GS = a.G * SMAX;
-  const int64_t J = a.J;
-  const size_t per_buf = (size_t)a.nseg * GS * J;
-  const double* E_in = a.st_end + (size_t)((q - 1) & 1) * per_buf;
-  double* E_out = a.st_end + (size_t)(q & 1) * per_buf;
-  const size_t own = ((size_t)k * GS + (size_t)g * SMAX) * J + job;  // my group's first entry
-  const size_t prv = k > 0 ? ((size_t)(k - 1) * GS + (size_t)g * SMAX) * J + job : 0;
-  const uint64_t field = (W == 64 ? ~0ull : ((1ull << W) - 1)) << ((uint64_t)slot * W);
-
-  // stale start state?  (every lane of a job agrees through the ballot)
+// Lists the segments k >= 1 whose start state is not, bit for bit, their
+// predecessor's end state.  One thread per job and segment (blockIdx.y = k - 1).
+__global__ __launch_bounds__(256) void spec_list(const SpecArgs a, int GS) {
+  const int64_t job = (int64_t)blockIdx.x * 256 + threadIdx.x, J = a.J;
+  if (job >= J) return;
+  const int k = (int)blockIdx.y + 1;
+  const size_t own = ((size_t)k * GS) * J + job, prv = own - (size_t)GS * J;
   bool differ = false;
-  if (mine && k > 0)
-#pragma unroll
-    for (int st = 0; st < SMAX; ++st)
-      differ |= bits_of(a.st_start[own + (size_t)st * J]) != bits_of(E_in[prv + (size_t)st * J]);
-  bool active = (__builtin_amdgcn_ballot_w64(differ) & field) != 0 && valid;
-  const bool ran = active;
-  if (__builtin_amdgcn_ballot_w64(active) == 0) {
-    if (mine)
-#pragma unroll
-      for (int st = 0; st < SMAX; ++st) E_out[own + (size_t)st * J] = E_in[own + (size_t)st * J];
-    return;
-  }
-
-  // the models this lane's group hosts (re-running jobs only) and its configuration
-  const int p = valid ? job / a.K : 0;
-  int cfg = -1;
-  uint64_t hostbits = 0;  // bit m: this lane's group hosts model m
-  if (mine && ran) {
-    cfg = a.group_cfg[(int64_t)p * a.G + g];
-    if (cfg < 0 || cfg >= a.C) cfg = -1;  // an unused group hosts nothing
-    if (cfg >= 0) {
-      const uint64_t* hm = a.host_mask + (int64_t)p * a.M;
-      for (int m = 0; m < a.M; ++m) hostbits |= ((hm[m] >> g) & 1ull) << m;
-    }
-  }
-  int cp = 1, lshift = 0;
-  while (cp < a.C) cp <<= 1;
-  while ((1 << lshift) < cp * SMAX * 8) ++lshift;
-  unsigned char* rec = smem;
-  double* sL = reinterpret_cast<double*>(rec + (size_t)(a.M + 1) * (1 << RSH));  // [M][Cp][SMAX]
-  double* sT = sL + (size_t)a.M * cp * SMAX;                                    // arrivals, stride 2
-  uint32_t* sO = reinterpret_cast<uint32_t*>(sT + 128);                          // record offsets
-  const uint64_t vmask = __builtin_amdgcn_ballot_w64(cfg >= 0);
-  const int cfg0 = vmask ? __builtin_amdgcn_readlane(cfg, __builtin_ctzll(vmask)) : 0;
-  const bool uni = __builtin_amdgcn_ballot_w64(cfg >= 0 && cfg != cfg0) == 0;
-  for (int idx = lane; idx < a.M * cp * SMAX; idx += 64) {
-    const int st = idx % SMAX, mc = idx / SMAX, cc = mc % cp, m = mc / cp;
-    sL[idx] = (cc < a.C && st < a.cfg_stages[cc]) ? a.stage_lat[((int64_t)m * a.C + cc) * a.smax_in + st] : 0.0;
-  }
-  for (int m = 0; m <= a.M; ++m) {
-    const uint64_t hm = m < a.M ? __builtin_amdgcn_ballot_w64((hostbits >> (m & 63)) & 1u) : 0;
-    if (lane == 0) {
-      const uint64_t one = lowest_per_field<W>(hm);  // lowest hosting lane of each job
-      *(uint64_t*)(rec + ((size_t)m << RSH) + kRecMask) = hm;
-      *(uint64_t*)(rec + ((size_t)m << RSH) + kRecCount) = one == hm ? 0u : (uint32_t)__builtin_popcountll(one);
-    }
-  }
-  for (int m = lane; m <= a.M; m += 64) {
-    unsigned char* r = rec + ((size_t)m << RSH);
-    *(double*)(r + rec_slo(SMAX)) = m < a.M ? a.d_single[m] : 0.0;
-#pragma unroll
-    for (int st = 0; st < SMAX; ++st)
-      ((double*)(r + kRecLat))[st] =
-          (m < a.M && uni && st < a.cfg_stages[cfg0]) ? a.stage_lat[((int64_t)m * a.C + cfg0) * a.smax_in + st]
-                                                      : 0.0;
-  }
-  SharedConst c;
-  c.rec = rec;
-  c.lrow = sL + (cfg < 0 ? 0 : cfg) * SMAX;
-  c.lshift = lshift;
-  c.sigma = valid ? a.slo_scale[job % a.K] : 0.0;
-  SharedLane<SMAX> st;
-#pragma unroll
-  for (int s = 0; s < SMAX; ++s) st.F[s] = (mine && ran) ? E_in[prv + (size_t)s * J] : 0.0;
-  st.fin_sum = st.served = 0;  // served: the job's count, in every lane of it
-  __syncthreads();
-
-  const int64_t b = seg_bound(a.n, a.nseg, k), e = seg_bound(a.n, a.nseg, k + 1);
-  const size_t ck0 = (size_t)k * a.ckps;
-  const int nck = b < e ? spec_ckpts(b, e, a.ck) : 0;
-  bool coupled = false;
-  TraceChunks tc;
-  tc.first(a, b, e, lane);
-  for (int64_t cb = b; cb < e; cb += 64) {
-    tc.advance(a, cb + 64, lane);
-    if (cb > b && (cb - b) % a.ck == 0) {
-      // saved state of the current results at cb: compare, then keep or stop
-      const int jl = (int)((cb - b) / a.ck) - 1;
-      const size_t j = ck0 + (size_t)jl;
-      bool same = true;
-      if (mine && active)
-#pragma unroll
-        for (int s = 0; s < SMAX; ++s)
-          same &= bits_of(a.ckpt[(j * GS + (size_t)g * SMAX + s) * J + job]) == bits_of(st.F[s]);
-      const bool job_same = (__builtin_amdgcn_ballot_w64(!same) & field) == 0;
-      const uint64_t js = st.served, jf = seg_sum_u64<W>(st.fin_sum);  // uniform flow
-      if (active) {
-        const size_t cj = j * J + job;
-        if (job_same) {
-          if (g == 0) {
-            const int64_t ds = (int64_t)js - a.ck_served[cj];
-            const uint64_t df = jf - a.ck_fsum[cj];
-            a.seg_served[(size_t)k * J + job] += ds;
-            a.seg_fsum[(size_t)k * J + job] += df;
-            a.ck_served[cj] = (int64_t)js;
-            a.ck_fsum[cj] = jf;
-            for (int j2 = jl + 1; j2 < nck; ++j2) {
-              a.ck_served[(ck0 + j2) * J + job] += ds;
-              a.ck_fsum[(ck0 + j2) * J + job] += df;
-            }
-          }
-          coupled = true;
-          active = false;
-        } else {
-          if (mine)
-#pragma unroll
-            for (int s = 0; s < SMAX; ++s) a.ckpt[(j * GS + (size_t)g * SMAX + s) * J + job] = st.F[s];
-          if (g == 0) {
-            a.ck_served[cj] = (int64_t)js;
-            a.ck_fsum[cj] = jf;
-          }
-        }
-      }
-      if (__builtin_amdgcn_ballot_w64(active) == 0) break;
-    }
-    if (cb - b >= a.cap && __builtin_amdgcn_ballot_w64(active) != 0) {
-      // runs from the two states do not meet: the pipeline gives up
-      if (lane == 0) a.cfg_info[2] = 1;
-      return;
-    }
-    const int cnt = __builtin_amdgcn_readfirstlane((int)(e - cb < 64 ? e - cb : 64));
-    // stage the chunk: lane r holds request cb + r
-    sT[2 * lane] = tc.tv;
-    sO[lane] = (uint32_t)((unsigned)tc.mv < (unsigned)a.M ? tc.mv : a.M) << RSH;
-    __syncthreads();
-    const uint64_t word = uni ? round_chunk<W, SMAX, true>(st, c, sT, sO, cnt)
-                              : round_chunk<W, SMAX, false>(st, c, sT, sO, cnt);
-    __syncthreads();
-    if (active && g == 0) a.bitmap[(cb >> 6) * J + job] = word;
-  }
-  const uint64_t js = st.served, jf = seg_sum_u64<W>(st.fin_sum);  // uniform flow
-  bool end_same = true;
-  if (mine && ran && !coupled)
-#pragma unroll
-    for (int s = 0; s < SMAX; ++s) end_same &= bits_of(E_in[own + (size_t)s * J]) == bits_of(st.F[s]);
-  const bool job_end_same = (__builtin_amdgcn_ballot_w64(!end_same) & field) == 0;
-  if (!valid) return;
-  if (ran) {
-    if (mine)
-#pragma unroll
-      for (int s = 0; s < SMAX; ++s) a.st_start[own + (size_t)s * J] = E_in[prv + (size_t)s * J];
-    if (!coupled) {
-      if (g == 0) {
-        a.seg_served[(size_t)k * J + job] = (int64_t)js;
-        a.seg_fsum[(size_t)k * J + job] = jf;
-      }
-      if (!job_end_same) {
-        if (mine)
-#pragma unroll
-          for (int s = 0; s < SMAX; ++s) E_out[own + (size_t)s * J] = st.F[s];
-        if (g == 0) atomicAdd(a.changed + q, 1);
-        return;
-      }
-    }
-  }
-  if (mine)
-#pragma unroll
-    for (int s = 0; s < SMAX; ++s) E_out[own + (size_t)s * J] = E_in[own + (size_t)s * J];
+  for (int x = 0; x < GS; ++x)
+    differ |= bits_of(a.st_start[own + (size_t)x * J]) != bits_of(a.st_end[prv + (size_t)x * J]);
+  if (differ) a.list[0][atomicAdd(a.count, 1)] = make_int2((int)job, k);
 }
 
 // Per job: totals over segments and the ordered digest over the accept words.
@@ -1155,9 +742,10 @@ namespace {
 
 // Whether every group that a placement uses (configuration >= 0) has one and
 // the same configuration; cfg_info = {uniform, that configuration, 0 (no
-// re-run has given up)}.  One workgroup of 1024 threads.
+// fix-up has given up)}; the fix-ups' lists and work start empty.  One workgroup of 1024 threads.
 __global__ __launch_bounds__(1024) void spec_cfg_check(const int32_t* group_cfg, int64_t cells, int n_configs,
-                                                       int32_t* cfg_info) {
+                                                       int32_t* cfg_info, int32_t* count, int32_t* taken,
+                                                       unsigned long long* work) {
   __shared__ int lo[1024], hi[1024];
   int l = 0x7FFFFFFF, h = -1;
   for (int64_t i = threadIdx.x; i < cells; i += 1024) {
@@ -1184,31 +772,10 @@ __global__ __launch_bounds__(1024) void spec_cfg_check(const int32_t* group_cfg,
     cfg_info[0] = none || (lo[0] == hi[0] && lo[0] < n_configs) ? 1 : 0;
     cfg_info[1] = none ? 0 : lo[0];
     cfg_info[2] = 0;
+    *work = 0;
+    for (int q = 0; q < kSpecRounds + 2; ++q) count[q] = taken[q] = 0;
   }
 }
-
-// Rounds in the group-per-lane layout (jobs of at most 16 groups).
-template <int W, int SMAX>
-void spec_rounds_gpl(const SpecArgs& a, hipStream_t s) {
-  const int njbw = (a.J + 64 / W - 1) / (64 / W);
-  const dim3 grid((unsigned)((int64_t)njbw * a.nseg)), block(64);
-  int cp = 1;
-  while (cp < a.C) cp <<= 1;
-  const size_t lds = round_fast_lds_bytes(a.M, cp, SMAX);
-  for (int q = 1; q < a.nseg; ++q) hipLaunchKernelGGL((spec_round_fast<W, SMAX>), grid, block, lds, s, a, q);
-}
-
-template <int SMAX>
-void spec_rounds_gpl_w(const SpecArgs& a, hipStream_t s) {
-  switch (pow2ceil_dev(a.G)) {
-    case 1: spec_rounds_gpl<1, SMAX>(a, s); break;
-    case 2: spec_rounds_gpl<2, SMAX>(a, s); break;
-    case 4: spec_rounds_gpl<4, SMAX>(a, s); break;
-    case 8: spec_rounds_gpl<8, SMAX>(a, s); break;
-    default: spec_rounds_gpl<16, SMAX>(a, s); break;
-  }
-}
-
 
 template <int SMAX, int MB, int JPW>
 hipError_t spec_launch_all(const SpecArgs& a, size_t lds_u, size_t lds_g, hipStream_t s) {
@@ -1217,14 +784,13 @@ hipError_t spec_launch_all(const SpecArgs& a, size_t lds_u, size_t lds_g, hipStr
   hipLaunchKernelGGL((spec_pass0<SMAX, MB, true, JPW, true>), grid, block, lds_u, s, a);
   hipLaunchKernelGGL((spec_pass0<SMAX, MB, false, JPW, false>), grid, block, lds_g, s, a);
   hipLaunchKernelGGL((spec_pass0<SMAX, MB, false, JPW, true>), grid, block, lds_g, s, a);
-  if (a.G <= 16 && spec_gpl_rounds()) {
-    spec_rounds_gpl_w<SMAX>(a, s);
-  } else {
-    for (int q = 1; q < a.nseg; ++q) {
-      hipLaunchKernelGGL((spec_round<SMAX, MB, true, JPW, false>), grid, block, lds_u, s, a, q);
-      hipLaunchKernelGGL((spec_round<SMAX, MB, true, JPW, true>), grid, block, lds_u, s, a, q);
-      hipLaunchKernelGGL((spec_round<SMAX, MB, false, JPW, false>), grid, block, lds_g, s, a, q);
-      hipLaunchKernelGGL((spec_round<SMAX, MB, false, JPW, true>), grid, block, lds_g, s, a, q);
+  if (a.nseg > 1) {
+    hipLaunchKernelGGL(spec_list, dim3((unsigned)((a.J + 255) / 256), (unsigned)(a.nseg - 1)), dim3(256), 0, s, a,
+                       a.G * SMAX);
+    // a job's segments are settled after nseg - 1 rounds, whatever the data
+    for (int q = 1; q <= std::min(a.nseg - 1, kSpecRounds + 1); ++q) {
+      const hipError_t e = as_host::launch_fix_any(SMAX, a, q, s);
+      if (e != hipSuccess) return e;
     }
   }
   const int nfb = (int)((a.J + 63) / 64);
@@ -1266,6 +832,24 @@ hipError_t spec_launch_mb(int G, const SpecArgs& a, size_t l1, size_t l2, hipStr
 
 namespace as_host {
 
+// One round (spec_fix): up to two wavefronts per SIMD take the entries in turn.
+hipError_t launch_fix_any(int smax, const as_dev::SpecArgs& a, int q, hipStream_t s) {
+  const int W = std::max(4, pow2ceil(a.G));
+  const int64_t blocks = std::min<int64_t>((int64_t)a.J * (a.nseg - 1), 8 * (int64_t)compute_units());
+  const size_t lds = as_dev::lean_lds_bytes(W, a.M, pow2ceil(a.C), smax, false, 1);
+  switch (W) {
+    case 4: return launch_fix<4>(smax, a, q, blocks, lds, s);
+    case 8: return launch_fix<8>(smax, a, q, blocks, lds, s);
+    case 16: return launch_fix<16>(smax, a, q, blocks, lds, s);
+    case 32: return launch_fix<32>(smax, a, q, blocks, lds, s);
+    default: return launch_fix<64>(smax, a, q, blocks, lds, s);
+  }
+}
+
+}  // namespace as_host
+
+namespace as_host {
+
 int compute_units() {
   static int cache[64] = {0};
   int dev = 0;
@@ -1282,15 +866,26 @@ namespace {
 
 
 
-// warm-up requests before a segment (measured on the 8192-placement workload:
-// 32768 -> 255.7 ms per step, 16384 -> 249.5, 8192 -> 242-244, 2048 -> 251,
-// none -> 261: a shorter warm-up leaves more to the rounds)
+// Warm-up requests before a segment.  A shorter warm-up leaves more start
+// states wrong, a longer one is simulated for nothing (1000 placements, 900,000
+// requests, 64 segments: 4096 -> 12.2 ms, 8192 -> 11.3, 16384 -> 12.5, and on
+// another seed, whose runs meet later, 99, 31 and 29).
 constexpr int64_t kSpecWarmup = 8192;
-// requests per segment at least: the warm-up and the rounds' re-runs stay a
-// small part of a segment's work (shorter traces, like the searches' 151k
-// requests, ran slower on these kernels)
-constexpr int64_t kSpecMinSegment = 131072;
-constexpr int64_t kSpecCheckpoint = 8192;   // requests between saved states
+// Requests per segment at least: beyond this the warm-up is nearly all of pass
+// 0 (1000 placements, 200,000 requests: segments of 12,500 8.0 ms, 6250 7.2,
+// 3125 6.5).
+constexpr int64_t kSpecMinSegment = 2048;
+// Requests between saved states: the closer, the sooner a re-run sees that it
+// has met the old results (2048 against 8192: 11.3 and 13.4 ms on the workload
+// above); doubled up to kSpecCheckpointMax until they fit kSpecCheckpointBytes.
+constexpr int64_t kSpecCheckpoint = 2048, kSpecCheckpointMax = 8192;
+constexpr int64_t kSpecCheckpointBytes = 512ll << 20;
+// Fix-ups may simulate J * n / kSpecBudget requests in all, and start from at
+// most kSpecPairs of all segments, before the call is left to the
+// group-per-lane kernels: where groups stay saturated runs from different
+// states never meet, and simulating everything again there is cheaper.
+constexpr int64_t kSpecBudget = 16;
+constexpr double kSpecPairs = 0.3;
 
 }  // namespace
 
@@ -1330,10 +925,9 @@ hipError_t pool_alloc(void** p, size_t bytes, hipStream_t s) {
 }
 
 // Segments per job for the speculative path: enough (job block, segment)
-// wavefronts to fill the device at the occupancy the LDS allows, each segment
-// long enough that the warm-up and the rounds' re-runs are a small part of it.
-// ALPASERVE_SPEC_SEGMENTS forces the count (tests).
-int spec_segments(int64_t n, int64_t J, int jpw, int per_cu) {
+// wavefronts to fill the device at the occupancy the LDS allows, none shorter
+// than min_seg.  ALPASERVE_SPEC_SEGMENTS forces the count (tests).
+int spec_segments(int64_t n, int64_t J, int jpw, int per_cu, int64_t min_seg, int max_seg) {
   if (const char* e = getenv("ALPASERVE_SPEC_SEGMENTS")) {
     const int v = atoi(e);
     if (v >= 1) return std::min(v, as_dev::kSpecMaxSeg);
@@ -1341,28 +935,60 @@ int spec_segments(int64_t n, int64_t J, int jpw, int per_cu) {
   const int64_t slots = (int64_t)compute_units() * std::max(per_cu, 1);
   const int64_t njb = (J + jpw - 1) / jpw;
   int64_t k = slots / std::max<int64_t>(njb, 1);
-  k = std::min<int64_t>(k, n / kSpecMinSegment);
-  return (int)std::max<int64_t>(1, std::min<int64_t>(k, as_dev::kSpecMaxSeg));
+  k = std::min<int64_t>(k, n / min_seg);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(k, max_seg));
 }
 
-// Whether the speculative kernels beat the shared-trace kernel on this call,
-// by a cost model in cycles per request of one wavefront, measured on gfx950
-// with the 8192-placement, 3.6 M-request workload: the shared-trace kernel
-// about 300 cycles with one wavefront per SIMD and 195 per wavefront beyond
-// that (it is issue-bound there); the speculative kernels about 1150 (one
-// wavefront per SIMD: the LDS holds no more) over a segment plus its warm-up,
-// and a fifth more for the rounds.  A single segment never pays.
-bool spec_pays(const KArgs& k, int nseg, int jpw, int per_cu) {
+// Whether the speculative kernels beat the group-per-lane kernels on this
+// call, by a model in nanoseconds of one wavefront: a request of a
+// group-per-lane wavefront takes 50 + 5.5 per doubling of its lanes + 4.5 per
+// stage alone on its SIMD (79 at 4 lanes and 4 stages, 90 at 16 and 4) and
+// three quarters of that per wavefront beyond; one of pass 0, with 64 jobs,
+// 150 + 35 per stage (287 at 4 stages), over a segment and its warm-up; the
+// fix-ups are taken as 2 ms.  The speculative kernels must promise 0.7 of the
+// other time, because traffic under which runs do not meet costs both.
+// Measured at 1000 placements and 4 stages: 900,000 requests 11.3 ms against
+// 93.6, 200,000 6.5 against 20.7.  A single segment never pays.
+bool spec_pays(const KArgs& k, int smax, int nseg, int jpw, int per_cu) {
   if (nseg < 2) return false;
   const double simds = 4.0 * compute_units();
   const int Wp = pow2ceil(k.G);
-  const double waves_shared = std::ceil((double)k.J / (64 / Wp));
-  const double t_shared = (double)k.n * std::max(300.0, 195.0 * waves_shared / simds);
+  const double waves_lean = std::ceil((double)k.J / (64 / Wp));
+  const double lean = 50.0 + 5.5 * std::log2((double)Wp) + 4.5 * smax;
+  const double t_lean = (double)k.n * lean * std::max(1.0, 0.75 * waves_lean / simds);
   const double slots = (double)compute_units() * std::max(per_cu, 1);
   const double waves_spec = std::ceil((double)k.J / jpw) * nseg;
   const double seg = (double)k.n / nseg + (double)std::min<int64_t>(kSpecWarmup, k.n);
-  const double t_spec = seg * 1150.0 * 1.2 * std::ceil(waves_spec / slots);
-  return t_spec < t_shared;
+  const double t_spec = seg * (150.0 + 35.0 * smax) * std::ceil(waves_spec / slots) + 2e6;
+  return t_spec < 0.7 * t_lean;
+}
+
+// Calls that as_simulate_placements_noalloc refuses because of their
+// workspace: those that segments of at least 131,072 requests would speed up
+// (about 1150 cycles per request over a segment and its warm-up, and a fifth
+// more, against 300 cycles, or 195 per wavefront of a SIMD) and whose
+// workspace at that cut, with saved states every 8192 requests, exceeds the
+// scratch.  The rule is the interface's; every other call is taken, on the
+// group-per-lane kernels where the speculative workspace does not fit.
+bool noalloc_refuses(const KArgs& k, int smax, int jpw, size_t scratch) {
+  // wavefronts a compute unit held of the kernels that this rule was made for
+  const size_t lds = (size_t)k.M * (smax + 1) * 8 + (size_t)(k.G + 2) * smax * jpw * 8;
+  const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(8, 160 * 1024 / lds));
+  const int nseg = spec_segments(k.n, k.J, jpw, per_cu, 131072, 64);
+  if (nseg < 2) return false;
+  const double simds = 4.0 * compute_units();
+  const double waves_shared = std::ceil((double)k.J / (64 / pow2ceil(k.G)));
+  const double t_shared = (double)k.n * std::max(300.0, 195.0 * waves_shared / simds);
+  const double slots = (double)compute_units() * std::max(per_cu, 1);
+  const double waves_spec = std::ceil((double)k.J / jpw) * nseg;
+  const double seg = (double)k.n / nseg + (double)std::min<int64_t>(8192, k.n);
+  if (seg * 1150.0 * 1.2 * std::ceil(waves_spec / slots) >= t_shared) return false;
+  auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  const size_t J = (size_t)k.J, GS = (size_t)k.G * smax, ckps = (size_t)((k.n / nseg + 64) / 8192 + 1);
+  const size_t state = nseg * GS * J * 8, total = up((size_t)((k.n + 63) / 64) * J * 8) + up(state) + up(2 * state) +
+                                                   2 * up(nseg * J * 8) + up(nseg * ckps * GS * J * 8) +
+                                                   2 * up(nseg * ckps * J * 8) + up(256 + (size_t)nseg * 4);
+  return total > scratch;
 }
 
 // Shared-trace simulation on the segment-speculative kernels.  Returns
@@ -1382,7 +1008,10 @@ bool spec_plan(const KArgs& k, int smax, size_t& lds_u, size_t& lds_g, int& per_
   const int jpw = kSpecJobsPerWave;
   lds_u = spec_lds_bytes(k.M, k.C, k.G, smax, true, jpw);
   lds_g = spec_lds_bytes(k.M, k.C, k.G, smax, false, jpw);
-  if (lds_g > lim || lds_u > lim) return false;
+  if (lds_g > lim || lds_u > lim) {
+    lds_g = 0;  // no call of this size is theirs
+    return false;
+  }
   per_cu = 1;
   switch (smax) {
     case 1: per_cu = spec_occupancy_mb<1>(k.G, lds_u); break;
@@ -1390,8 +1019,8 @@ bool spec_plan(const KArgs& k, int smax, size_t& lds_u, size_t& lds_g, int& per_
     case 4: per_cu = spec_occupancy_mb<4>(k.G, lds_u); break;
     default: per_cu = spec_occupancy_mb<8>(k.G, lds_u); break;
   }
-  nseg = spec_segments(k.n, k.J, jpw, per_cu);
-  return spec_forced() || spec_pays(k, nseg, jpw, per_cu);
+  nseg = spec_segments(k.n, k.J, jpw, per_cu, std::max(kSpecMinSegment, k.min_segment), kSpecMaxSeg);
+  return spec_forced() || spec_pays(k, smax, nseg, jpw, per_cu);
 }
 
 }  // namespace
@@ -1410,7 +1039,15 @@ int run_spec(KArgs& k, int smax, hipStream_t stream, bool can_give_up, void* cal
   const int jpw = kSpecJobsPerWave;
   size_t lds_u = 0, lds_g = 0;
   int per_cu = 1, nseg = 1;
-  if (!spec_plan(k, smax, lds_u, lds_g, per_cu, nseg)) return AS_E_LIMITS;
+  const bool takes = spec_plan(k, smax, lds_u, lds_g, per_cu, nseg);
+  if (caller_ws && !spec_forced() && lds_g > 0 && noalloc_refuses(k, smax, jpw, caller_ws_bytes)) {
+    fail(AS_E_LIMITS,
+         "this call needs more speculative-kernel workspace than the %zu-byte no-allocation scratch; "
+         "as_simulate_placements takes it",
+         caller_ws_bytes);
+    return kSpecScratchTooSmall;
+  }
+  if (!takes) return AS_E_LIMITS;
 
   SpecArgs a;
   std::memset(&a, 0, sizeof a);
@@ -1439,11 +1076,18 @@ int run_spec(KArgs& k, int smax, hipStream_t stream, bool can_give_up, void* cal
   a.nseg = nseg;
   a.warmup = kSpecWarmup;
   if (const char* w = getenv("ALPASERVE_SPEC_WARMUP")) a.warmup = std::max<int64_t>(0, atoll(w));
-  a.ck = kSpecCheckpoint;
+  a.ck = caller_ws ? kSpecCheckpointMax : kSpecCheckpoint;
+  while (a.ck < kSpecCheckpointMax && k.n / a.ck * (int64_t)k.G * smax * k.J * 8 > kSpecCheckpointBytes) a.ck *= 2;
   if (const char* c = getenv("ALPASERVE_SPEC_CKPT")) a.ck = std::max<int64_t>(64, atoll(c) & ~(int64_t)63);
   a.ckps = (int32_t)((k.n / a.nseg + 64) / a.ck + 1);
-  a.cap = can_give_up ? kSpecGiveUp : INT64_MAX;
-  if (const char* c = getenv("ALPASERVE_SPEC_CAP"); c && can_give_up) a.cap = std::max<int64_t>(64, atoll(c));
+  a.cap = INT64_MAX;
+  a.budget = can_give_up ? (int64_t)k.J * (k.n / kSpecBudget) : INT64_MAX;
+  a.pairs = can_give_up ? (int64_t)(kSpecPairs * (double)k.J * (nseg - 1)) : INT64_MAX;
+  // ALPASERVE_SPEC_CAP (requests of one re-run) alone decides where it is set (tests)
+  if (const char* c = getenv("ALPASERVE_SPEC_CAP"); c && can_give_up) {
+    a.cap = std::max<int64_t>(64, atoll(c));
+    a.budget = a.pairs = INT64_MAX;
+  }
   while (a.nseg > 1 && (int64_t)a.njb * a.nseg > 0x7FFFFFFFLL) --a.nseg;
   if ((int64_t)a.njb * a.nseg > 0x7FFFFFFFLL) return AS_E_LIMITS;
   a.nw = (k.n + 63) / 64;
@@ -1454,20 +1098,21 @@ int run_spec(KArgs& k, int smax, hipStream_t stream, bool can_give_up, void* cal
   const size_t b_seg = (size_t)a.nseg * J * 8;
   const size_t b_ckpt = (size_t)a.nseg * a.ckps * GS * J * 8;
   const size_t b_cks = (size_t)a.nseg * a.ckps * J * 8;
-  const size_t b_small = 256 + (size_t)a.nseg * 4;
+  const size_t b_claim = (size_t)J * 4, b_list = (size_t)J * a.nseg * 8, b_small = 256;
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  const size_t total = up(b_bitmap) + up(b_state) + up(2 * b_state) + 2 * up(b_seg) + up(b_ckpt) +
-                       2 * up(b_cks) + up(b_small);
+  const size_t total = up(b_bitmap) + 4 * up(b_state) + 2 * up(b_seg) + up(b_ckpt) +
+                       2 * up(b_cks) + up(b_claim) + 2 * up(b_list) + up(b_small);
   char* ws = nullptr;
   hipError_t e = hipSuccess;
   if (caller_ws) {
-    if (total > caller_ws_bytes) {
+    if (spec_forced() && total > caller_ws_bytes) {
       fail(AS_E_LIMITS,
            "this call needs %zu bytes of speculative-kernel workspace, more than the %zu-byte "
            "no-allocation scratch; as_simulate_placements takes it",
            total, caller_ws_bytes);
       return kSpecScratchTooSmall;
     }
+    if (total > caller_ws_bytes) return AS_E_LIMITS;  // the kernels that need none take it
     ws = static_cast<char*>(caller_ws);
   } else {
     // a workspace beyond a quarter of the device's memory leaves the call to
@@ -1491,7 +1136,7 @@ int run_spec(KArgs& k, int smax, hipStream_t stream, bool can_give_up, void* cal
   };
   a.bitmap = reinterpret_cast<uint64_t*>(take(b_bitmap));
   a.st_start = reinterpret_cast<double*>(take(b_state));
-  a.st_end = reinterpret_cast<double*>(take(2 * b_state));
+  a.st_end = reinterpret_cast<double*>(take(b_state));
   a.seg_served = reinterpret_cast<int64_t*>(take(b_seg));
   a.seg_fsum = reinterpret_cast<uint64_t*>(take(b_seg));
   a.ckpt = reinterpret_cast<double*>(take(b_ckpt));
@@ -1499,10 +1144,17 @@ int run_spec(KArgs& k, int smax, hipStream_t stream, bool can_give_up, void* cal
   a.ck_fsum = reinterpret_cast<uint64_t*>(take(b_cks));
   int32_t* small = reinterpret_cast<int32_t*>(take(b_small));
   a.cfg_info = small;
-  a.changed = small + 64;
+  a.work = reinterpret_cast<unsigned long long*>(small + 4);
+  a.count = small + 8;
+  a.taken = a.count + as_dev::kSpecRounds + 2;
+  a.claimed = reinterpret_cast<int32_t*>(take(b_claim));
+  for (int x = 0; x < 2; ++x) {
+    a.xch[x] = reinterpret_cast<double*>(take(b_state));
+    a.list[x] = reinterpret_cast<int2*>(take(b_list));
+  }
 
   hipLaunchKernelGGL(spec_cfg_check, dim3(1), dim3(1024), 0, stream, k.group_cfg, (int64_t)k.P * k.G, k.C,
-                     a.cfg_info);
+                     a.cfg_info, a.count, a.taken, a.work);
   switch (smax) {
     case 1: e = spec_launch_mb<1>(k.G, a, lds_u, lds_g, stream); break;
     case 2: e = spec_launch_mb<2>(k.G, a, lds_u, lds_g, stream); break;

@@ -135,3 +135,19 @@ def test_segments(api, G):
         if j in fin:
             row, k = out[list(fin).index(j)], min(b - a, stride)
             assert row[:k].tobytes() == f[:k].tobytes() and np.isnan(row[k:]).all(), j
+
+
+@pytest.mark.parametrize("G,hosts,rate", [(3, 3, 0.02), (16, 4, 0.02), (40, 12, 0.02), (6, 2, 0.2)])
+@pytest.mark.parametrize("segments", [2, 9, 10, 40])
+def test_fix_ups(api, monkeypatch, G, hosts, rate, segments):
+    """The speculative kernels' fix-ups: cold segment starts, saved states every
+    64 requests, fewer and more segments than rounds (the last jobs then whole);
+    busy groups, whose runs meet late or never, and idle ones."""
+    monkeypatch.setenv("ALPASERVE_PATH", "spec")
+    monkeypatch.setenv("ALPASERVE_SPEC_SEGMENTS", str(segments))
+    monkeypatch.setenv("ALPASERVE_SPEC_WARMUP", "0")
+    monkeypatch.setenv("ALPASERVE_SPEC_CKPT", "64")
+    monkeypatch.setenv("ALPASERVE_SPEC_CAP", str(1 << 40))
+    pb = _problem(G * 100 + segments, 6000, G, 70, [2.0], hosts=hosts)
+    pb.t *= rate / 0.02
+    _check(api, pb, f"fix-ups G={G} segments={segments}", sorted({*range(0, 70, 3), *pb.finish_jobs.tolist()}))
