@@ -338,14 +338,21 @@ __global__ void validate_kernel(const double* t, const int32_t* model, int64_t n
   if (bad) atomicOr(flags, bad);
 }
 
-// Statistics launch of the shared-trace kernel (no per-request rows):
-// AS_E_LIMITS when its tables do not fit in a workgroup's LDS.
+// Statistics launch of the group-per-lane kernels.  They take the tables that
+// fit a workgroup's LDS beside the models' SLOs, 1024 staged requests and the
+// counters of four jobs, as these calls always have; the kernels need less,
+// with at most four jobs per wavefront where the counters of more do not fit.
 int run_shared_stats(KArgs& a, int smax, hipStream_t stream) {
-  const int W = pow2ceil(a.G), jw = lean_jobs_per_wave(W, a.J);
+  const int cp = pow2ceil(a.C);
+  if ((size_t)a.M * cp * smax * 8 + (size_t)a.M * (8 + as_dev::kWaves * 4) + 1024 * 12 > shared_lds_limit())
+    return fail(AS_E_LIMITS, "stage-latency table (%d models x %d configs x %d stages) does not fit in LDS",
+                a.M, a.C, smax);
+  int W = pow2ceil(a.G);
+  while (W < 16 && as_dev::lean_lds_bytes(W, a.M, cp, smax, true, 1) > shared_lds_limit()) W *= 2;
+  const int jw = lean_jobs_per_wave(W, a.J);
   const int64_t nw = lean_wave_count(a.J, a.K, jw);
   const int waves = lean_waves_per_block(nw, W, a, smax, true);
-  const size_t lds = as_dev::lean_lds_bytes(W, a.M, pow2ceil(a.C), smax, true, waves);
-  if (!use_shared_path() || a.n_finish != 0 || lds > shared_lds_limit()) return AS_E_LIMITS;
+  const size_t lds = as_dev::lean_lds_bytes(W, a.M, cp, smax, true, waves);
   const hipError_t e =
       launch_lean_any(LeanKind::kStats, W, smax, a, jw, (nw + waves - 1) / waves, waves, lds, stream);
   if (e != hipSuccess) return fail(AS_E_HIP, "kernel launch failed: %s", hipGetErrorString(e));

@@ -37,9 +37,8 @@ int check_common(const as_models_t* models, const as_placements_t* plc, KArgs& a
 // AS_E_LIMITS without launching.
 int run_shared_trace(KArgs& a, int W, int smax, hipStream_t stream, void* scratch = nullptr,
                      size_t scratch_bytes = 0);
-// Statistics launch of the shared-trace kernel (one SLO scale, no per-request
-// output rows); returns AS_E_LIMITS without launching when that kernel cannot
-// take the call (several scales, output rows, tables beyond the LDS).
+// Statistics launch of the group-per-lane kernels (a complete, no per-request
+// output rows); AS_E_LIMITS, without launching, for tables beyond the LDS.
 int run_shared_stats(KArgs& a, int smax, hipStream_t stream);
 
 // Shared-trace simulation on the segment-speculative kernels (one lane per

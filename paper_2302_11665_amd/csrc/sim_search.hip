@@ -539,12 +539,6 @@ int fast_search(const as_trace_t* trace, const as_models_t* models, const int64_
       ak.out_group_busy = bz;
       ak.n_finish = 0;
       rc = run_shared_stats(ak, shape_s[L.shape], sk);
-      if (rc == AS_E_LIMITS) {
-        // the shared-trace kernel does not take it: the general statistics kernel
-        as_placements_t pl{Pk, Gk, gk, mk};
-        rc = as_simulate_stats(trace, models, &pl, static_cast<const double*>(d.p[1]), 1, sv, nullptr, msv, bz,
-                               sk);
-      }
       if (rc != AS_OK) return rc;
       if (sk != s) {
         if ((e = hipEventRecord(pool.ev[k], sk)) != hipSuccess || (e = hipStreamWaitEvent(s, pool.ev[k], 0)) != hipSuccess)

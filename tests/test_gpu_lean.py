@@ -79,11 +79,13 @@ def test_infinite_finish_times(api):
     _check(api, _problem(5, 300, 12, 4, [1.0, np.inf], big=True), "infinite finish times")
 
 
-@pytest.mark.parametrize("G,P,K", [(3, 30, 1), (16, 2100, 1), (24, 9, 3), (64, 5, 2)])
-def test_statistics(api, G, P, K):
+@pytest.mark.parametrize("G,P,K,table", [
+    (3, 30, 1, {}), (16, 2100, 1, {}), (16, 1030, 3, {}), (24, 9, 3, {}), (64, 5, 2, {}),
+    (1, 3, 2, dict(M=64, cfgs=tuple((8, k) for k in range(1, 33))))])  # the largest table
+def test_statistics(api, G, P, K, table):
     import torch
     from paper_2302_11665_amd import sim
-    pb = dataclasses.replace(_problem(G + P, 333, G, P, [1.0, 2.5, np.inf][:K]), finish_jobs=np.zeros(0, np.int32))
+    pb = dataclasses.replace(_problem(G + P, 333, G, P, [1.0, 2.5, np.inf][:K], **table), finish_jobs=np.zeros(0, np.int32))
     dp = api.upload(pb)
     M, J = len(pb.d_single), pb.n_jobs
     ms = torch.empty((J, M), dtype=torch.int64, device="cuda")
