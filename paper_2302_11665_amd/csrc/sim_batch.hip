@@ -22,12 +22,13 @@
 // time and index, SLO); the trace is read 64 requests at a time into
 // registers.  Every decision is wave-uniform: the next idle group is a
 // butterfly min over the lanes with queued work, the model with the oldest
-// queued head a scalar pass over lane reads, and the batch size one pass in
-// which lane l runs the chain of a batch of l + 1 requests.  Only the
-// stage-latency table sits in LDS, so every job of a launch is resident at
-// once.  The arithmetic is the definition's (no FMA, v_max_f64, the batch
-// factor rounded once), so served counts, digests and finish times are
-// bit-identical to a sequential evaluation.
+// queued head a minimum over the model lanes, and the batch size one pass in
+// which lane l runs the chain of a batch of l + 1 requests.  In LDS are the
+// stage-latency table and, per model, a ring of its newest queued requests,
+// small enough that every job of a launch is resident at once.  The
+// arithmetic is the definition's (no FMA, v_max_f64, the batch factor rounded
+// once), so served counts, digests and finish times are bit-identical to a
+// sequential evaluation.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -78,7 +79,7 @@ struct BatchArgs {
   const uint32_t* li;
   const uint64_t* lmix;
   double beta;
-  int32_t M, C, smax_in, G, K, J, max_batch, qcap, n_finish;
+  int32_t M, C, smax_in, G, K, J, max_batch, qcap, ring, n_finish;  // ring: entries per model (0, 8, 16 or 32)
   int32_t cfg_stages[AS_MAX_CONFIGS];
   int32_t finish_jobs[AS_MAX_FINISH];
 };
@@ -184,19 +185,68 @@ __global__ __launch_bounds__(64) void list_fill(const ListArgs a) {
   });
 }
 
-// LDS of one job: the stage-latency table [M][Cp][SMAX].
-__host__ __device__ constexpr size_t batch_lds_bytes(int M, int Cp, int SMAX) {
-  return (size_t)M * Cp * SMAX * 8;
+// LDS of one job: the stage-latency table [M][Cp][SMAX], then per model a ring
+// of its R last queued requests (arrival times, then trace indices).
+__host__ __device__ constexpr size_t batch_lds_bytes(int M, int Cp, int SMAX, int R) {
+  return (size_t)M * Cp * SMAX * 8 + (size_t)M * R * 12;
+}
+
+// Smallest key over the job's W lanes, in each of them.
+template <int W>
+__device__ __forceinline__ double batch_min(double v) {
+  v = seg_min<16>(v);
+  if constexpr (W >= 32) {
+    const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    v = vmin(__hiloint2double((int)h[0], (int)l[0]), __hiloint2double((int)h[1], (int)l[1]));
+  }
+  if constexpr (W >= 64) {
+    const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    v = vmin(__hiloint2double((int)h[0], (int)l[0]), __hiloint2double((int)h[1], (int)l[1]));
+  }
+  return v;
+}
+
+using LdsF64 = __attribute__((address_space(3))) double;
+using LdsU32 = __attribute__((address_space(3))) uint32_t;
+
+// Smallest of 64 lanes' values, uniform: one DPP minimum per row of 16 lanes,
+// then the four rows in scalar registers.
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
+  v = std::min(v, dpp_u32<kXor1>(v));
+  v = std::min(v, dpp_u32<kXor2>(v));
+  v = std::min(v, dpp_u32<kHalfMirror>(v));
+  v = std::min(v, dpp_u32<kMirror>(v));
+  const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)v, 0), r1 = (uint32_t)__builtin_amdgcn_readlane((int)v, 16);
+  const uint32_t r2 = (uint32_t)__builtin_amdgcn_readlane((int)v, 32), r3 = (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
+  return std::min(std::min(r0, r1), std::min(r2, r3));
 }
 
 // W: lanes reduced per job, the group count rounded up to a power of two (at
 // least 16, so the reductions inside a 16-lane row are DPP only).
+//
+// What bounds it is one wavefront's chain of dependent instructions and
+// branches per request, not throughput: 2048 jobs are two wavefronts a SIMD.
+// So a request's hosts, deadline and digest term are gathered 64 requests at a
+// time; masks stay in scalar registers and reductions run only when a ballot
+// is not empty; the oldest queued head is one DPP minimum; commits are selects;
+// and the queues' newest entries are in LDS, because a new head read from the
+// lists (L2) was waited for by the next event.  Measured: 256 placements of 16
+// four-stage groups x 8 scales, 76,800 requests: 84.7 ms a call before, 67.0
+// with this.
 template <int W, int SMAX>
 __global__ __launch_bounds__(64) void batch_kernel(const BatchArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   int cp = 1;
   while (cp < a.C) cp <<= 1;
   double* sL = reinterpret_cast<double*>(smem);  // [M][cp][SMAX]
+  const int nL = a.M * cp * SMAX;
+  // the rings; with none (R = 0) slot 0 of the table stands in for reads that are not used
+  const uint32_t R = (uint32_t)a.ring, rmask = R ? R - 1 : 0;
+  // (LDS pointers by type: a generic one would merge with the list reads into flat loads)
+  LdsF64* rt = (LdsF64*)(sL + (R ? nL : 0));
+  LdsU32* ri = (LdsU32*)(rt + (size_t)a.M * R);
   const int lane = threadIdx.x;
   const int64_t job = blockIdx.x;
   const int p = (int)(job / a.K);
@@ -204,12 +254,12 @@ __global__ __launch_bounds__(64) void batch_kernel(const BatchArgs a) {
 
   int cfg = lane < a.G ? a.group_cfg[(int64_t)p * a.G + lane] : -1;
   if (cfg >= a.C || cfg < 0) cfg = -1;
+  const uint64_t exists = __builtin_amdgcn_ballot_w64(cfg >= 0);
   uint64_t hostbits = 0;  // bit m: this lane's group hosts model m
   if (cfg >= 0) {
     const uint64_t* hm = a.host_mask + (int64_t)p * a.M;
     for (int m = 0; m < a.M; ++m) hostbits |= ((hm[m] >> lane) & 1u) << m;
   }
-  const int nL = a.M * cp * SMAX;
   for (int idx = lane; idx < nL; idx += 64) {
     const int s = idx % SMAX;
     const int mc = idx / SMAX;
@@ -223,9 +273,10 @@ __global__ __launch_bounds__(64) void batch_kernel(const BatchArgs a) {
   double* frowp = frow >= 0 ? a.out_finish + (int64_t)frow * a.n : nullptr;
   __syncthreads();
 
-  // lane m: model m's SLO and queue, the run [qh, qt) of its list starting
-  // at loff, with the head's arrival time and trace index
+  // lane m: the groups that host model m, its SLO and its queue, the run
+  // [qh, qt) of its list starting at loff, with the head's time and index
   const bool mlane = lane < a.M;
+  const uint64_t hostm = mlane ? a.host_mask[(int64_t)p * a.M + lane] & exists : 0ull;
   const double slo = mlane ? sigma * a.d_single[lane] : 0.0;
   const uint32_t loff = mlane ? a.off[lane] : 0u;
   uint32_t qh = 0, qt = 0, qidx = 0;
@@ -233,43 +284,39 @@ __global__ __launch_bounds__(64) void batch_kernel(const BatchArgs a) {
   uint64_t nonempty = 0;  // bit m: model m has queued requests (wave-uniform)
 
   const double* lbase = sL + (size_t)(cfg < 0 ? 0 : cfg) * SMAX;  // + m * cp * SMAX
+  const double facl = 1.0 + a.beta * (double)lane;                // factor of a batch of lane + 1
   double F[SMAX];
 #pragma unroll
   for (int s = 0; s < SMAX; ++s) F[s] = 0.0;
-  uint64_t h = 0, fin_sum = 0;  // wave-uniform parts of the digest
-  uint64_t hl = 0, pend = 0;    // per-lane digest terms of batched requests (pend: the last batch's, in flight)
+  uint64_t fin_sum = 0, finl = 0;  // finish bits of batches (uniform) and of single requests (per lane)
+  uint64_t hl = 0;                 // per-lane digest terms
+  // indices of batched requests, in lanes below pfill; their terms are
+  // computed when no more fit
+  uint32_t pidx = 0, pfill = 0;
   int64_t served = 0;
   uint32_t flags = 0;
   const double kInf = __builtin_inf();
 
-  // every lane's chain, through its own group, for one request of model m
-  // started at x; returns the last stage's finish, fs[] its stage finishes
-  auto chain1 = [&](int m, double x, double (&fs)[SMAX]) {
-    const double fac = 1.0 + a.beta * 0.0;
-    const double* L = lbase + (size_t)m * cp * SMAX;
-    double f = x;
-#pragma unroll
-    for (int s = 0; s < SMAX; ++s) {
-      fs[s] = vmax(f, F[s]) + L[s] * fac;
-      f = fs[s];
-    }
-    return f;
-  };
-  // smallest key over the job's lanes (lane 0's segment), wave-uniform
-  auto wave_min = [&](double key) {
-    const double v = seg_min<W>(key);
-    return rl_f64(v, 0);
-  };
-  // model mc's queue head moves to list position hn (< tail: its entry is
-  // loaded by lane mc; the value is first needed at the next decision)
+  // model mc's queue [.., tl) has its head moved to list position hn.  Every
+  // queued request was written to the ring when it joined, so the newest R
+  // are there; older ones are read from the arrival lists.
   auto set_head = [&](int mc, uint32_t hn, uint32_t tl) {
-    if (lane == mc) qh = hn;
-    if (hn == tl) {
-      nonempty &= ~(1ull << mc);
-    } else if (lane == mc) {
-      qht = a.lt[loff + hn];
-      qidx = a.li[loff + hn];
+    double nt;
+    uint32_t ni;
+    if (__builtin_expect(tl - hn <= R, 1)) {
+      const uint32_t slot = (uint32_t)mc * R + (hn & rmask);
+      nt = rt[slot];
+      ni = ri[slot];
+    } else {
+      const uint32_t pos = (uint32_t)__builtin_amdgcn_readlane((int)loff, mc) + hn;
+      nt = a.lt[pos];
+      ni = a.li[pos];
     }
+    const bool own = lane == mc;
+    qh = own ? hn : qh;
+    qht = own ? nt : qht;
+    qidx = own ? ni : qidx;
+    nonempty = hn == tl ? nonempty & ~(1ull << mc) : nonempty;
   };
 
   // the trace, 64 requests per register chunk, the next chunk in flight
@@ -287,42 +334,43 @@ __global__ __launch_bounds__(64) void batch_kernel(const BatchArgs a) {
   for (int64_t base = 0; base <= a.n; base += 64) {
     const int cnt = (int)((a.n - base) < 64 ? (a.n - base) : 64);
     if (base + 64 < a.n) load_chunk(base + 64, tvn, mvn, ovn);
+    // lane e: request e's model, hosts (none for a model out of range),
+    // deadline and digest term
+    const bool mok = (unsigned)mv < (unsigned)a.M;
+    const int mrow = mok ? mv : 0;
+    const auto gather = [&](int v) { return __builtin_amdgcn_ds_bpermute(mrow << 2, v); };
+    const uint32_t hlo = (uint32_t)gather((int)(uint32_t)hostm), hhi = (uint32_t)gather((int)(uint32_t)(hostm >> 32));
+    const uint64_t hmv = mok ? ((uint64_t)hhi << 32) | hlo : 0ull;
+    const double dlv = tv + __hiloint2double(gather(__double2hiint(slo)), gather(__double2loint(slo)));
+    const uint64_t mixv = mix64((uint64_t)(base + lane));
+    uint64_t okm = 0;  // bit e: request e was served at its arrival
     // cnt requests of this chunk, then (after the last one) the final drain
     const int steps = base + 64 > a.n ? cnt + 1 : cnt;
     for (int e = 0; e < steps; ++e) {
       const bool last = e == cnt;
-      const int64_t i = base + e;
-      const double horizon = last ? 0.0 : rl_f64(tv, e);
+      const double ti = last ? kInf : rl_f64(tv, e);
+      const int m = __builtin_amdgcn_readlane(mrow, e);
+      double Lm[SMAX];  // of the request's model on every lane's group
+#pragma unroll
+      for (int s = 0; s < SMAX; ++s) Lm[s] = lbase[(size_t)m * cp * SMAX + s];
       // idle events up to the arrival (all remaining ones after the last)
       for (;;) {
-        const bool work = cfg >= 0 && (hostbits & nonempty) != 0;
-        const double key = work ? F[0] : kInf;
-        const double mn = wave_min(key);
-        const uint64_t wm = __builtin_amdgcn_ballot_w64(work && key == mn);
-        if (wm == 0) break;
-        if (!last && !(mn <= horizon)) break;
-        const int g = __builtin_ctzll(wm);
+        const uint64_t evm = __builtin_amdgcn_ballot_w64((hostbits & nonempty) != 0) & __builtin_amdgcn_ballot_w64(F[0] <= ti);
+        if (evm == 0) break;
+        const double emin = batch_min<W>(__builtin_amdgcn_inverse_ballot_w64(evm) ? F[0] : kInf);
+        const int g = __builtin_ctzll(__builtin_amdgcn_ballot_w64(F[0] == emin) & evm);
         const uint64_t ghost = rl_u64(hostbits, g);
         const int gcfg = __builtin_amdgcn_readlane(cfg, g);
         double Fg[SMAX];
 #pragma unroll
         for (int s = 0; s < SMAX; ++s) Fg[s] = rl_f64(F[s], g);
+        const double mn = Fg[0];
         for (;;) {
-          uint64_t cand = ghost & nonempty;
+          const uint64_t cand = ghost & nonempty;
           if (cand == 0) break;  // nothing left for this group: it stays idle
           // the queued model whose head has the lowest trace index
-          int mc = __builtin_ctzll(cand);
-          uint32_t hidx = (uint32_t)__builtin_amdgcn_readlane((int)qidx, mc);
-          cand &= cand - 1;
-          while (cand) {
-            const int m = __builtin_ctzll(cand);
-            cand &= cand - 1;
-            const uint32_t r = (uint32_t)__builtin_amdgcn_readlane((int)qidx, m);
-            if (r < hidx) {
-              mc = m;
-              hidx = r;
-            }
-          }
+          const uint32_t hidx = wave_min_u32(__builtin_amdgcn_inverse_ballot_w64(cand) ? qidx : 0xFFFFFFFFu);
+          const int mc = __builtin_ctzll(__builtin_amdgcn_ballot_w64(qidx == hidx) & cand);
           const uint32_t h0 = (uint32_t)__builtin_amdgcn_readlane((int)qh, mc);
           const uint32_t tl = (uint32_t)__builtin_amdgcn_readlane((int)qt, mc);
           const double dl = rl_f64(qht + slo, mc);  // the head's deadline
@@ -332,49 +380,54 @@ __global__ __launch_bounds__(64) void batch_kernel(const BatchArgs a) {
           // a time, lane l the size p0 + l + 1, and the first size that
           // misses ends the search (as trying them one by one would)
           const double* L = sL + ((size_t)mc * cp + gcfg) * SMAX;
-          int b = 0;
-          double fin = 0.0;
-          double fsel[SMAX];
-#pragma unroll
-          for (int s = 0; s < SMAX; ++s) fsel[s] = 0.0;
-          for (int p0 = 0; p0 < bmax; p0 += 64) {
-            const int bb = p0 + lane + 1;
-            const double fac = 1.0 + a.beta * (double)(bb - 1);
+          auto sizes = [&](int p0, double fac, double (&fs)[SMAX]) {  // how many of p0 + 1 .. p0 + 64 meet it
             double f = mn;
-            double fs[SMAX];
 #pragma unroll
             for (int s = 0; s < SMAX; ++s) {
               fs[s] = vmax(f, Fg[s]) + L[s] * fac;
               f = fs[s];
             }
-            const uint64_t miss = __builtin_amdgcn_ballot_w64(bb <= bmax && f > dl);
-            const int lim = bmax - p0 < 64 ? bmax - p0 : 64;
-            const int nok = miss ? __builtin_ctzll(miss) : lim;  // sizes p0+1 .. p0+nok meet it
-            if (nok > 0) {
-              b = p0 + nok;
-              fin = rl_f64(f, nok - 1);
-#pragma unroll
-              for (int s = 0; s < SMAX; ++s) fsel[s] = rl_f64(fs[s], nok - 1);
-            }
-            if (nok < 64) break;
-          }
+            const int lim = bmax - p0;
+            const uint64_t stop = __builtin_amdgcn_ballot_w64(f > dl) | (lim < 64 ? ~0ull << lim : 0ull);
+            return stop ? __builtin_ctzll(stop) : 64;
+          };
+          double fs[SMAX], fsel[SMAX];
+          int b = sizes(0, facl, fs);
           if (b == 0) {
             // the head cannot meet its deadline: dropped (its output stays -1)
             set_head(mc, h0 + 1, tl);
             continue;
           }
-          if (lane == g) {
 #pragma unroll
-            for (int s = 0; s < SMAX; ++s) F[s] = fsel[s];
+          for (int s = 0; s < SMAX; ++s) fsel[s] = rl_f64(fs[s], b - 1);
+          if (__builtin_expect(b == 64 && bmax > 64, 0)) {
+            for (int p0 = 64; p0 < bmax; p0 += 64) {
+              const int nok = sizes(p0, 1.0 + a.beta * (double)(p0 + lane), fs);
+              if (nok == 0) break;
+              b = p0 + nok;
+#pragma unroll
+              for (int s = 0; s < SMAX; ++s) fsel[s] = rl_f64(fs[s], nok - 1);
+              if (nok < 64) break;
+            }
           }
-          // the batch's digest terms: the first 64 arrive while the
-          // simulation goes on and are added at the next batch
+          const double fin = fsel[SMAX - 1];
+#pragma unroll
+          for (int s = 0; s < SMAX; ++s) F[s] = lane == g ? fsel[s] : F[s];
+          // the batch's digest terms
           const uint32_t lb0 = (uint32_t)__builtin_amdgcn_readlane((int)loff, mc) + h0;
-          hl += pend;
-          pend = 0;
-          if (lane < b) pend = a.lmix[lb0 + lane];
-          for (int k0 = 64; k0 < b; k0 += 64)
-            if (k0 + lane < b) hl += a.lmix[lb0 + k0 + lane];
+          if (__builtin_expect(avail <= R, 1)) {
+            if (pfill + (uint32_t)b > 64) {
+              hl += (uint32_t)lane < pfill ? mix64(pidx) : 0ull;
+              pfill = 0;
+            }
+            const uint32_t k = (uint32_t)lane - pfill;
+            const uint32_t v = ri[(uint32_t)mc * R + ((h0 + k) & rmask)];
+            pidx = k < (uint32_t)b ? v : pidx;
+            pfill += (uint32_t)b;
+          } else {
+            for (int k0 = 0; k0 < b; k0 += 64)
+              if (k0 + lane < b) hl += a.lmix[lb0 + k0 + lane];
+          }
           fin_sum += (uint64_t)b * (uint64_t)__double_as_longlong(fin);
           served += b;
           if (frowp) {
@@ -387,29 +440,29 @@ __global__ __launch_bounds__(64) void batch_kernel(const BatchArgs a) {
       }
       if (last) break;
       // the arrival
-      const double ti = horizon;
-      const int m0 = __builtin_amdgcn_readlane(mv, e);
-      const bool mok = (unsigned)m0 < (unsigned)a.M;
-      const int m = mok ? m0 : 0;
-      const bool hosted = mok && cfg >= 0 && ((hostbits >> m) & 1u);
-      if (__builtin_amdgcn_ballot_w64(hosted) == 0) continue;  // no group hosts it: a miss
-      const bool avail = hosted && F[0] <= ti;
-      const uint64_t av = __builtin_amdgcn_ballot_w64(avail);
-      if (av != 0) {
-        const double key = avail ? F[0] : kInf;
-        const double mn = wave_min(key);
-        const int ga = __builtin_ctzll(__builtin_amdgcn_ballot_w64(avail && key == mn));
+      const uint64_t hm = rl_u64(hmv, e);
+      if (hm == 0) continue;  // no group hosts it: a miss
+      const uint64_t avm = __builtin_amdgcn_ballot_w64(F[0] <= ti) & hm;
+      if (avm != 0) {
+        // the hosting group that has been idle longest, ties to the lowest
+        const double amin = batch_min<W>(__builtin_amdgcn_inverse_ballot_w64(avm) ? F[0] : kInf);
+        const uint64_t tie = __builtin_amdgcn_ballot_w64(F[0] == amin) & avm;
+        // every lane's chain through its own group (the factor of one request is 1)
         double fs[SMAX];
-        const double fl = rl_f64(chain1(m, ti, fs), ga);
-        if (!(fl > ti + rl_f64(slo, m))) {
-          if (lane == ga) {
+        double f = ti;
 #pragma unroll
-            for (int s = 0; s < SMAX; ++s) F[s] = fs[s];
-          }
-          served += 1;
-          h += mix64((uint64_t)i);
-          fin_sum += (uint64_t)__double_as_longlong(fl);
-          if (frowp && lane == 0) frowp[i] = fl;
+        for (int s = 0; s < SMAX; ++s) {
+          fs[s] = vmax(f, F[s]) + Lm[s];
+          f = fs[s];
+        }
+        const uint64_t acc = __builtin_amdgcn_ballot_w64(!(f > rl_f64(dlv, e))) & (tie & (0 - tie));
+        const bool mine = __builtin_amdgcn_inverse_ballot_w64(acc);
+#pragma unroll
+        for (int s = 0; s < SMAX; ++s) F[s] = mine ? fs[s] : F[s];
+        finl += mine ? (uint64_t)__double_as_longlong(f) : 0ull;
+        okm |= (uint64_t)(acc != 0) << e;
+        if (frowp) {
+          if (mine) frowp[base + e] = f;
         }
       } else {
         // Queue heads of model m that can no longer be served are dropped
@@ -421,47 +474,81 @@ __global__ __launch_bounds__(64) void batch_kernel(const BatchArgs a) {
         // bound is dropped by the definition too, and dropping it earlier
         // changes no other decision.  This keeps each queue to the requests
         // that are still servable.
-        double lbv = ti;
-        {
-          const double* L = lbase + (size_t)m * cp * SMAX;
-#pragma unroll
-          for (int s = 0; s < SMAX; ++s) lbv = lbv + L[s];
-        }
-        const double lb = wave_min(hosted ? lbv : kInf);
         const uint32_t rank = (uint32_t)__builtin_amdgcn_readlane((int)ov, e);
-        uint32_t hd = (uint32_t)__builtin_amdgcn_readlane((int)qh, m);
+        const uint32_t h0 = (uint32_t)__builtin_amdgcn_readlane((int)qh, m);
         const uint32_t tl = (uint32_t)__builtin_amdgcn_readlane((int)qt, m);
-        while (hd != tl && rl_f64(qht + slo, m) < lb) {
-          ++hd;
-          set_head(m, hd, tl);
-        }
-        if (hd == tl) {
-          // an empty queue: request i becomes its head
-          if (lane == m) {
-            qh = rank;
-            qht = ti;
-            qidx = (uint32_t)i;
+        uint32_t hd = h0;
+        if (hd != tl) {
+          double lbv = ti;
+#pragma unroll
+          for (int s = 0; s < SMAX; ++s) lbv = lbv + Lm[s];
+          const double lb = rl_f64(batch_min<W>(__builtin_amdgcn_inverse_ballot_w64(hm) ? lbv : kInf), 0);
+          if (rl_f64(qht + slo, m) < lb) {
+            // 64 entries at a time, lane l the one at hd + l; the first that
+            // is kept is the new head
+            const double slom = rl_f64(slo, m);
+            const uint32_t lm = (uint32_t)__builtin_amdgcn_readlane((int)loff, m);
+            do {
+              const uint32_t left = tl - hd;
+              double nt;
+              uint32_t ni;
+              if (left <= R) {
+                const uint32_t slot = (uint32_t)m * R + ((hd + (uint32_t)lane) & rmask);
+                nt = rt[slot];
+                ni = ri[slot];
+              } else {
+                const uint32_t pos = lm + hd + std::min((uint32_t)lane, left - 1);
+                nt = a.lt[pos];
+                ni = a.li[pos];
+              }
+              const uint64_t keep = __builtin_amdgcn_ballot_w64(!(nt + slom < lb)) & (left < 64 ? ~(~0ull << left) : ~0ull);
+              if (keep) {
+                const int k = __builtin_ctzll(keep);
+                hd += (uint32_t)k;
+                const double kt = rl_f64(nt, k);
+                const uint32_t ki = (uint32_t)__builtin_amdgcn_readlane((int)ni, k);
+                qh = lane == m ? hd : qh;
+                qht = lane == m ? kt : qht;
+                qidx = lane == m ? ki : qidx;
+                break;
+              }
+              hd += std::min(left, 64u);
+            } while (hd != tl);
           }
-        } else {
+        }
+        const bool own = lane == m;
+        const bool first = own && hd == tl;  // an empty queue: request i becomes its head
+        qh = first ? rank : qh;
+        qht = first ? ti : qht;
+        qidx = first ? (uint32_t)(base + e) : qidx;
+        if (hd != tl) {
           if (rank != tl) flags |= 2u;  // not the run's next arrival (cannot happen by the rules)
           if (tl - hd >= (uint32_t)a.qcap) flags |= 1u;  // past the capacity: the results are incomplete
         }
-        if (lane == m) qt = rank + 1;
+        qt = own ? rank + 1 : qt;
         nonempty |= 1ull << m;
+        if (R) {  // every lane writes the same words, so every lane may read them
+          const uint32_t slot = (uint32_t)m * R + (rank & rmask);
+          rt[slot] = ti;
+          ri[slot] = (uint32_t)(base + e);
+        }
       }
     }
+    hl += (okm >> lane) & 1 ? mixv : 0ull;
+    served += __builtin_popcountll(okm);
     tv = tvn;
     mv = mvn;
     ov = ovn;
   }
-  hl += pend;
+  hl += (uint32_t)lane < pfill ? mix64(pidx) : 0ull;
   const uint64_t hsum = seg_sum_u64<64>(hl);
+  const uint64_t fsum = seg_sum_u64<64>(finl);
   if (lane == 0) {
     if (flags) atomicOr(a.flags, flags);
     a.out_served[job] = served;
     if (a.out_digest) {
-      a.out_digest[2 * job] = h + hsum;
-      a.out_digest[2 * job + 1] = fin_sum;
+      a.out_digest[2 * job] = hsum;
+      a.out_digest[2 * job + 1] = fin_sum + fsum;
     }
   }
 }
@@ -525,10 +612,20 @@ extern "C" int as_simulate_batched(const as_trace_t* trace, const as_models_t* m
       if (finish_jobs[q] == finish_jobs[f]) return fail(AS_E_INVALID_ARG, "finish_jobs[%d] repeats job %d", f, finish_jobs[f]);
     a.finish_jobs[f] = finish_jobs[f];
   }
-  const size_t lds = as_dev::batch_lds_bytes(ka.M, pow2ceil(ka.C), smax);
-  if (lds > shared_lds_limit())
-    return fail(AS_E_LIMITS, "batched: the stage-latency table needs %zu bytes of LDS (> %zu)", lds,
+  const int cp = pow2ceil(ka.C);
+  const size_t table = as_dev::batch_lds_bytes(ka.M, cp, smax, 0);
+  if (table > shared_lds_limit())
+    return fail(AS_E_LIMITS, "batched: the stage-latency table needs %zu bytes of LDS (> %zu)", table,
                 shared_lds_limit());
+  // Entries of each model's LDS ring: as many as leave all jobs resident (up to
+  // 16 wavefronts a compute unit), 8 at least, none where the table leaves no
+  // room.  A queue longer than its ring reads the lists, which costs an L2
+  // access instead of an LDS one.
+  const int64_t per_cu = std::min<int64_t>((J + 255) / 256, 16);
+  int ring = 32;
+  while (ring > 8 && as_dev::batch_lds_bytes(ka.M, cp, smax, ring) * per_cu > 160 * 1024) ring /= 2;
+  while (ring > 0 && as_dev::batch_lds_bytes(ka.M, cp, smax, ring) > shared_lds_limit()) ring = ring > 8 ? ring / 2 : 0;
+  const size_t lds = as_dev::batch_lds_bytes(ka.M, cp, smax, ring);
   if (J == 0) return ok();
   hipStream_t s = (hipStream_t)stream;
   a.t = trace->t;
@@ -551,6 +648,7 @@ extern "C" int as_simulate_batched(const as_trace_t* trace, const as_models_t* m
   a.J = (int32_t)J;
   a.max_batch = max_batch;
   a.qcap = queue_cap;
+  a.ring = ring;
   a.n_finish = n_finish;
   for (int c = 0; c < AS_MAX_CONFIGS; ++c) a.cfg_stages[c] = ka.cfg_stages[c];
   // one workspace: the flags word, then the per-model arrival lists

@@ -175,3 +175,27 @@ def test_batching_every_lane_twice(dev):
     say("every lane twice", G, M, n)
     served, digest, fin = _run(dev, t, model, d, cs, L, gc, hm, scales, 4, 0.5, [0, 3])
     _check(oracle.lib(), t, model, d, cs, L, gc, hm, scales, 4, 0.5, served, digest, fin, [0, 3])
+
+
+@pytest.mark.parametrize("G,Smax,M,C,P,B", [(2, 1, 2, 1, 3, 1), (2, 2, 3, 2, 3, 33), (3, 8, 64, 16, 4, 40),
+                                            (20, 2, 64, 2, 4, 5), (4, 1, 64, 1, 1300, 7)])
+def test_batching_queues_past_the_ring(dev, G, Smax, M, C, P, B):
+    """Bursts on a few of the models, so that their queues grow past the 8 to
+    32 entries kept in LDS and are served, and dropped, from both sides of
+    that line: few models, a large latency table, 64 models on 20 groups, and
+    so many jobs that the rings are at their smallest."""
+    rng = np.random.default_rng(7000 + M * 31 + G)
+    n = 700 if P < 100 else 260
+    t = np.sort(np.concatenate([np.repeat(rng.uniform(0.0, 20.0, 2), n // 4), rng.uniform(0.0, 30.0, n - 2 * (n // 4))]))
+    model = np.where(rng.random(n) < 0.8, rng.integers(0, min(M, 3), n), rng.integers(0, M, n)).astype(np.int32)
+    cs = rng.integers(1, Smax + 1, C).astype(np.int32)
+    cs[0] = Smax
+    L = rng.uniform(0.01, 0.2, (M, C, Smax))
+    d = L[:, 0, :].sum(axis=1)
+    gc = rng.integers(0, C, (P, G)).astype(np.int32)
+    hm = rng.integers(1, 1 << G, (P, M)).astype(np.uint64)
+    scales = [4.0, 40.0, INF]
+    fj = [0, 1, 2, P * 3 - 1]
+    say("past the ring", G, Smax, M, C, P, B)
+    served, digest, fin = _run(dev, t, model, d, cs, L, gc, hm, scales, B, 0.01, fj)
+    _check(oracle.lib(), t, model, d, cs, L, gc, hm, scales, B, 0.01, served, digest, fin, fj)
