@@ -945,10 +945,13 @@ int spec_segments(int64_t n, int64_t J, int jpw, int per_cu, int64_t min_seg, in
 // stage alone on its SIMD (79 at 4 lanes and 4 stages, 90 at 16 and 4) and
 // three quarters of that per wavefront beyond; one of pass 0, with 64 jobs,
 // 150 + 35 per stage (287 at 4 stages), over a segment and its warm-up; the
-// fix-ups are taken as 2 ms.  The speculative kernels must promise 0.7 of the
-// other time, because traffic under which runs do not meet costs both.
-// Measured at 1000 placements and 4 stages: 900,000 requests 11.3 ms against
-// 93.6, 200,000 6.5 against 20.7.  A single segment never pays.
+// fix-ups are taken as 2 ms.  The speculative kernels must promise 0.4 of the
+// other time, because traffic under which runs do not meet costs both: 777
+// late selections of 32 two-stage groups, 76,801 requests, promise 0.64 and do
+// not meet, which took 11.1 ms against 7.2 on the group-per-lane kernels alone.
+// Measured at 1000 placements and 4 stages, which promise 0.1 and 0.3: 900,000
+// requests 11.3 ms against 93.6, 200,000 6.5 against 20.7.  A single segment
+// never pays.
 bool spec_pays(const KArgs& k, int smax, int nseg, int jpw, int per_cu) {
   if (nseg < 2) return false;
   const double simds = 4.0 * compute_units();
@@ -960,7 +963,7 @@ bool spec_pays(const KArgs& k, int smax, int nseg, int jpw, int per_cu) {
   const double waves_spec = std::ceil((double)k.J / jpw) * nseg;
   const double seg = (double)k.n / nseg + (double)std::min<int64_t>(kSpecWarmup, k.n);
   const double t_spec = seg * (150.0 + 35.0 * smax) * std::ceil(waves_spec / slots) + 2e6;
-  return t_spec < 0.7 * t_lean;
+  return t_spec < 0.4 * t_lean;
 }
 
 // Calls that as_simulate_placements_noalloc refuses because of their
