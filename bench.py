@@ -58,7 +58,8 @@ HBM_PEAK = 8.0e12
 # change, traffic is reported as null until it is measured again.
 KERNEL_SOURCES = ["paper_2302_11665_amd/csrc/sim_api.hip", "paper_2302_11665_amd/csrc/sim_kernel.hpp",
                   "paper_2302_11665_amd/csrc/sim_launch.hip", "paper_2302_11665_amd/csrc/sim_launch.hpp",
-                  "paper_2302_11665_amd/csrc/sim_shared.hpp", "paper_2302_11665_amd/csrc/sim_spec.hip"]
+                  "paper_2302_11665_amd/csrc/sim_lean.hpp", "paper_2302_11665_amd/csrc/sim_shared.hpp",
+                  "paper_2302_11665_amd/csrc/sim_spec.hip", "paper_2302_11665_amd/csrc/sim_spec.hpp"]
 MEASURED_TRAFFIC = {
     "sources_sha256": "684637c3137697b219070a57f8d6c86345014f155cb72e55f014cddc6114a889",
     # one step of the heavy-trace workload runs the segment-speculative

@@ -76,7 +76,7 @@ __device__ __forceinline__ int spec_ckpts(int64_t b, int64_t e, int64_t ck) { re
 // replaced.  A run that never meets them replaces the segment, and the next
 // segment is looked at again.
 //
-// Rounds (spec_round) take all listed segments of all jobs at once, each from
+// Rounds (round_entry) take all listed segments of all jobs at once, each from
 // the end state its predecessor had after the round before, so that a job
 // whose runs meet slowly settles all its segments in about (requests until
 // they meet) / (segment length) rounds: after kSpecRounds of them few jobs are

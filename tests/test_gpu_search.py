@@ -52,8 +52,7 @@ def _stats_case(rng, G, Smax, M, n):
     return t, model, d_single, cfg_stages, L, group_cfg, host_mask, scales
 
 
-# one scale runs the shared-trace kernel's statistics mode, several scales the
-# statistics kernel
+# the group-per-lane kernels' statistics mode, with one scale and with several
 @pytest.mark.parametrize("one_scale", [True, False])
 @pytest.mark.parametrize("G,Smax", [(1, 1), (3, 2), (16, 4), (17, 3), (40, 8), (64, 1)])
 def test_stats_kernel_matches_oracle(dev, G, Smax, one_scale):
