@@ -116,11 +116,14 @@ int as_simulate_placements(const as_trace_t* trace, const as_models_t* models,
  * (code under HIP graph capture, tight serving loops, hosts that forbid
  * allocation): the same arguments, kernels and results, bit for bit, but no
  * hipMalloc, hipFree or other allocating call is made.  Where the speculative
- * kernels take the call (long traces), their workspace (accept bits and saved
- * states, about 0.19 bytes per request x job) comes from an array of
+ * kernels take the call (longer traces), their workspace (an accept bit per
+ * request x job, and saved states) comes from an array of
  * AS_NOALLOC_SCRATCH_BYTES in device memory that the library holds on every
- * device it runs on until the process ends; a call whose workspace would be
- * larger returns AS_E_LIMITS without launching anything (as_simulate_placements
+ * device it runs on until the process ends; the trace is cut into as many
+ * segments as fit it.  A call that segments of 131,072 requests would speed up
+ * and whose workspace at that cut, with states saved every 8192 requests,
+ * exceeds the array returns AS_E_LIMITS without launching anything (1000 jobs of
+ * 16 four-stage groups: beyond 1.3 million requests; as_simulate_placements
  * takes such calls).  Every call on one device shares that device's array, and
  * the array keeps the last call's contents (each call initialises what it
  * reads), so calls that overlap on one device -- on different streams, or

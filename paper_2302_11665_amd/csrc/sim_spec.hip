@@ -966,6 +966,8 @@ bool spec_pays(const KArgs& k, int smax, int nseg, int jpw, int per_cu) {
   return t_spec < 0.4 * t_lean;
 }
 
+size_t ws_up(size_t x) { return (x + 255) & ~(size_t)255; }
+
 // Calls that as_simulate_placements_noalloc refuses because of their
 // workspace: those that segments of at least 131,072 requests would speed up
 // (about 1150 cycles per request over a segment and its warm-up, and a fifth
@@ -986,11 +988,11 @@ bool noalloc_refuses(const KArgs& k, int smax, int jpw, size_t scratch) {
   const double waves_spec = std::ceil((double)k.J / jpw) * nseg;
   const double seg = (double)k.n / nseg + (double)std::min<int64_t>(8192, k.n);
   if (seg * 1150.0 * 1.2 * std::ceil(waves_spec / slots) >= t_shared) return false;
-  auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const size_t J = (size_t)k.J, GS = (size_t)k.G * smax, ckps = (size_t)((k.n / nseg + 64) / 8192 + 1);
-  const size_t state = nseg * GS * J * 8, total = up((size_t)((k.n + 63) / 64) * J * 8) + up(state) + up(2 * state) +
-                                                   2 * up(nseg * J * 8) + up(nseg * ckps * GS * J * 8) +
-                                                   2 * up(nseg * ckps * J * 8) + up(256 + (size_t)nseg * 4);
+  const size_t state = nseg * GS * J * 8;
+  const size_t total = ws_up((size_t)((k.n + 63) / 64) * J * 8) + ws_up(state) + ws_up(2 * state) +
+                       2 * ws_up(nseg * J * 8) + ws_up(nseg * ckps * GS * J * 8) + 2 * ws_up(nseg * ckps * J * 8) +
+                       ws_up(256 + (size_t)nseg * 4);
   return total > scratch;
 }
 
@@ -1002,36 +1004,69 @@ bool noalloc_refuses(const KArgs& k, int smax, int jpw, size_t scratch) {
 // gated fallback kernels read the give-up flag in it, then release it.
 namespace {
 
-// Whether the speculative kernels take the call (sizes, LDS, segments that
-// pay or are forced), with their LDS sizes, occupancy and segment count.
-bool spec_plan(const KArgs& k, int smax, size_t& lds_u, size_t& lds_g, int& per_cu, int& nseg) {
+// How a call is cut: segments, requests between saved states, saved states per
+// segment, and the bytes of each workspace array.
+struct SpecPlan {
+  size_t lds_u = 0, lds_g = 0;
+  int per_cu = 1, nseg = 1, ckps = 0;
+  int64_t ck = 0;
+  size_t bitmap = 0, state = 0, seg = 0, ckpt = 0, cks = 0, claim = 0, list = 0, small = 256, total = 0;
+};
+
+void spec_sizes(const KArgs& k, int smax, int nseg, SpecPlan& p) {
+  const size_t J = (size_t)k.J, GS = (size_t)k.G * smax;
+  p.nseg = nseg;
+  p.ckps = (int)((k.n / nseg + 64) / p.ck + 1);
+  p.bitmap = (size_t)((k.n + 63) / 64) * J * 8;
+  p.state = nseg * GS * J * 8;
+  p.seg = nseg * J * 8;
+  p.ckpt = (size_t)nseg * p.ckps * GS * J * 8;
+  p.cks = (size_t)nseg * p.ckps * J * 8;
+  p.claim = J * 4;
+  p.list = J * nseg * 8;
+  p.total = ws_up(p.bitmap) + 4 * ws_up(p.state) + 2 * ws_up(p.seg) + ws_up(p.ckpt) + 2 * ws_up(p.cks) +
+            ws_up(p.claim) + 2 * ws_up(p.list) + ws_up(p.small);
+}
+
+// Whether the speculative kernels take the call (sizes, LDS, segments that pay
+// or are forced), and how they cut it.  scratch: bytes of a caller's workspace,
+// 0 where it is allocated.  A trace is cut into as many segments as fill the
+// device; where their workspace exceeds the scratch, into as many as fit, which
+// must still pay: 1000 placements of 16 four-stage groups, 900,000 requests, fit
+// 256 MiB with 32 segments instead of 64.
+bool spec_plan(const KArgs& k, int smax, size_t scratch, SpecPlan& p) {
   using namespace as_dev;
   if (k.n <= 0 || k.J <= 0) return false;
   const size_t lim = shared_lds_limit();
   const int jpw = kSpecJobsPerWave;
-  lds_u = spec_lds_bytes(k.M, k.C, k.G, smax, true, jpw);
-  lds_g = spec_lds_bytes(k.M, k.C, k.G, smax, false, jpw);
-  if (lds_g > lim || lds_u > lim) {
-    lds_g = 0;  // no call of this size is theirs
+  p.lds_u = spec_lds_bytes(k.M, k.C, k.G, smax, true, jpw);
+  p.lds_g = spec_lds_bytes(k.M, k.C, k.G, smax, false, jpw);
+  if (p.lds_g > lim || p.lds_u > lim) {
+    p.lds_g = 0;  // no call of this size is theirs
     return false;
   }
-  per_cu = 1;
   switch (smax) {
-    case 1: per_cu = spec_occupancy_mb<1>(k.G, lds_u); break;
-    case 2: per_cu = spec_occupancy_mb<2>(k.G, lds_u); break;
-    case 4: per_cu = spec_occupancy_mb<4>(k.G, lds_u); break;
-    default: per_cu = spec_occupancy_mb<8>(k.G, lds_u); break;
+    case 1: p.per_cu = spec_occupancy_mb<1>(k.G, p.lds_u); break;
+    case 2: p.per_cu = spec_occupancy_mb<2>(k.G, p.lds_u); break;
+    case 4: p.per_cu = spec_occupancy_mb<4>(k.G, p.lds_u); break;
+    default: p.per_cu = spec_occupancy_mb<8>(k.G, p.lds_u); break;
   }
-  nseg = spec_segments(k.n, k.J, jpw, per_cu, std::max(kSpecMinSegment, k.min_segment), kSpecMaxSeg);
-  return spec_forced() || spec_pays(k, smax, nseg, jpw, per_cu);
+  int nseg = spec_segments(k.n, k.J, jpw, p.per_cu, std::max(kSpecMinSegment, k.min_segment), kSpecMaxSeg);
+  while (nseg > 1 && (int64_t)((k.J + jpw - 1) / jpw) * nseg > 0x7FFFFFFFLL) --nseg;
+  p.ck = scratch ? kSpecCheckpointMax : kSpecCheckpoint;
+  while (p.ck < kSpecCheckpointMax && k.n / p.ck * (int64_t)k.G * smax * k.J * 8 > kSpecCheckpointBytes) p.ck *= 2;
+  if (const char* c = getenv("ALPASERVE_SPEC_CKPT")) p.ck = std::max<int64_t>(64, atoll(c) & ~(int64_t)63);
+  spec_sizes(k, smax, nseg, p);
+  while (scratch && p.total > scratch && p.nseg > 1 && !getenv("ALPASERVE_SPEC_SEGMENTS"))
+    spec_sizes(k, smax, p.nseg - 1, p);
+  return spec_forced() || spec_pays(k, smax, p.nseg, jpw, p.per_cu);
 }
 
 }  // namespace
 
 bool spec_takes(const KArgs& k, int smax) {
-  size_t lds_u = 0, lds_g = 0;
-  int per_cu = 1, nseg = 1;
-  return spec_plan(k, smax, lds_u, lds_g, per_cu, nseg);
+  SpecPlan p;
+  return spec_plan(k, smax, 0, p);
 }
 
 int run_spec(KArgs& k, int smax, hipStream_t stream, bool can_give_up, void* caller_ws,
@@ -1040,13 +1075,12 @@ int run_spec(KArgs& k, int smax, hipStream_t stream, bool can_give_up, void* cal
   *workspace = nullptr;
   *gave_up = nullptr;
   const int jpw = kSpecJobsPerWave;
-  size_t lds_u = 0, lds_g = 0;
-  int per_cu = 1, nseg = 1;
-  const bool takes = spec_plan(k, smax, lds_u, lds_g, per_cu, nseg);
-  if (caller_ws && !spec_forced() && lds_g > 0 && noalloc_refuses(k, smax, jpw, caller_ws_bytes)) {
+  SpecPlan pl;
+  const bool takes = spec_plan(k, smax, caller_ws ? caller_ws_bytes : 0, pl);
+  if (caller_ws && !spec_forced() && pl.lds_g > 0 && noalloc_refuses(k, smax, jpw, caller_ws_bytes)) {
     fail(AS_E_LIMITS,
-         "this call needs more speculative-kernel workspace than the %zu-byte no-allocation scratch; "
-         "as_simulate_placements takes it",
+         "this call, cut into segments of 131072 requests, needs more speculative-kernel workspace than the "
+         "%zu-byte no-allocation scratch; as_simulate_placements takes it",
          caller_ws_bytes);
     return kSpecScratchTooSmall;
   }
@@ -1076,35 +1110,23 @@ int run_spec(KArgs& k, int smax, hipStream_t stream, bool can_give_up, void* cal
   std::memcpy(a.cfg_stages, k.cfg_stages, sizeof a.cfg_stages);
   std::memcpy(a.finish_jobs, k.finish_jobs, sizeof a.finish_jobs);
   a.njb = (int32_t)((k.J + jpw - 1) / jpw);
-  a.nseg = nseg;
+  a.nseg = pl.nseg;
   a.warmup = kSpecWarmup;
   if (const char* w = getenv("ALPASERVE_SPEC_WARMUP")) a.warmup = std::max<int64_t>(0, atoll(w));
-  a.ck = caller_ws ? kSpecCheckpointMax : kSpecCheckpoint;
-  while (a.ck < kSpecCheckpointMax && k.n / a.ck * (int64_t)k.G * smax * k.J * 8 > kSpecCheckpointBytes) a.ck *= 2;
-  if (const char* c = getenv("ALPASERVE_SPEC_CKPT")) a.ck = std::max<int64_t>(64, atoll(c) & ~(int64_t)63);
-  a.ckps = (int32_t)((k.n / a.nseg + 64) / a.ck + 1);
+  a.ck = pl.ck;
+  a.ckps = (int32_t)pl.ckps;
   a.cap = INT64_MAX;
   a.budget = can_give_up ? (int64_t)k.J * (k.n / kSpecBudget) : INT64_MAX;
-  a.pairs = can_give_up ? (int64_t)(kSpecPairs * (double)k.J * (nseg - 1)) : INT64_MAX;
+  a.pairs = can_give_up ? (int64_t)(kSpecPairs * (double)k.J * (a.nseg - 1)) : INT64_MAX;
   // ALPASERVE_SPEC_CAP (requests of one re-run) alone decides where it is set (tests)
   if (const char* c = getenv("ALPASERVE_SPEC_CAP"); c && can_give_up) {
     a.cap = std::max<int64_t>(64, atoll(c));
     a.budget = a.pairs = INT64_MAX;
   }
-  while (a.nseg > 1 && (int64_t)a.njb * a.nseg > 0x7FFFFFFFLL) --a.nseg;
   if ((int64_t)a.njb * a.nseg > 0x7FFFFFFFLL) return AS_E_LIMITS;
   a.nw = (k.n + 63) / 64;
 
-  const int64_t J = k.J, GS = (int64_t)k.G * smax;
-  const size_t b_bitmap = (size_t)a.nw * J * 8;
-  const size_t b_state = (size_t)a.nseg * GS * J * 8;
-  const size_t b_seg = (size_t)a.nseg * J * 8;
-  const size_t b_ckpt = (size_t)a.nseg * a.ckps * GS * J * 8;
-  const size_t b_cks = (size_t)a.nseg * a.ckps * J * 8;
-  const size_t b_claim = (size_t)J * 4, b_list = (size_t)J * a.nseg * 8, b_small = 256;
-  auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  const size_t total = up(b_bitmap) + 4 * up(b_state) + 2 * up(b_seg) + up(b_ckpt) +
-                       2 * up(b_cks) + up(b_claim) + 2 * up(b_list) + up(b_small);
+  const size_t total = pl.total;
   char* ws = nullptr;
   hipError_t e = hipSuccess;
   if (caller_ws) {
@@ -1134,35 +1156,35 @@ int run_spec(KArgs& k, int smax, hipStream_t stream, bool can_give_up, void* cal
   size_t off = 0;
   auto take = [&](size_t bytes) {
     char* p = ws + off;
-    off += up(bytes);
+    off += ws_up(bytes);
     return p;
   };
-  a.bitmap = reinterpret_cast<uint64_t*>(take(b_bitmap));
-  a.st_start = reinterpret_cast<double*>(take(b_state));
-  a.st_end = reinterpret_cast<double*>(take(b_state));
-  a.seg_served = reinterpret_cast<int64_t*>(take(b_seg));
-  a.seg_fsum = reinterpret_cast<uint64_t*>(take(b_seg));
-  a.ckpt = reinterpret_cast<double*>(take(b_ckpt));
-  a.ck_served = reinterpret_cast<int64_t*>(take(b_cks));
-  a.ck_fsum = reinterpret_cast<uint64_t*>(take(b_cks));
-  int32_t* small = reinterpret_cast<int32_t*>(take(b_small));
+  a.bitmap = reinterpret_cast<uint64_t*>(take(pl.bitmap));
+  a.st_start = reinterpret_cast<double*>(take(pl.state));
+  a.st_end = reinterpret_cast<double*>(take(pl.state));
+  a.seg_served = reinterpret_cast<int64_t*>(take(pl.seg));
+  a.seg_fsum = reinterpret_cast<uint64_t*>(take(pl.seg));
+  a.ckpt = reinterpret_cast<double*>(take(pl.ckpt));
+  a.ck_served = reinterpret_cast<int64_t*>(take(pl.cks));
+  a.ck_fsum = reinterpret_cast<uint64_t*>(take(pl.cks));
+  int32_t* small = reinterpret_cast<int32_t*>(take(pl.small));
   a.cfg_info = small;
   a.work = reinterpret_cast<unsigned long long*>(small + 4);
   a.count = small + 8;
   a.taken = a.count + as_dev::kSpecRounds + 2;
-  a.claimed = reinterpret_cast<int32_t*>(take(b_claim));
+  a.claimed = reinterpret_cast<int32_t*>(take(pl.claim));
   for (int x = 0; x < 2; ++x) {
-    a.xch[x] = reinterpret_cast<double*>(take(b_state));
-    a.list[x] = reinterpret_cast<int2*>(take(b_list));
+    a.xch[x] = reinterpret_cast<double*>(take(pl.state));
+    a.list[x] = reinterpret_cast<int2*>(take(pl.list));
   }
 
   hipLaunchKernelGGL(spec_cfg_check, dim3(1), dim3(1024), 0, stream, k.group_cfg, (int64_t)k.P * k.G, k.C,
                      a.cfg_info, a.count, a.taken, a.work);
   switch (smax) {
-    case 1: e = spec_launch_mb<1>(k.G, a, lds_u, lds_g, stream); break;
-    case 2: e = spec_launch_mb<2>(k.G, a, lds_u, lds_g, stream); break;
-    case 4: e = spec_launch_mb<4>(k.G, a, lds_u, lds_g, stream); break;
-    default: e = spec_launch_mb<8>(k.G, a, lds_u, lds_g, stream); break;
+    case 1: e = spec_launch_mb<1>(k.G, a, pl.lds_u, pl.lds_g, stream); break;
+    case 2: e = spec_launch_mb<2>(k.G, a, pl.lds_u, pl.lds_g, stream); break;
+    case 4: e = spec_launch_mb<4>(k.G, a, pl.lds_u, pl.lds_g, stream); break;
+    default: e = spec_launch_mb<8>(k.G, a, pl.lds_u, pl.lds_g, stream); break;
   }
   if (e != hipSuccess || !can_give_up) {
     const hipError_t ef = caller_ws ? hipSuccess : hipFreeAsync(ws, stream);

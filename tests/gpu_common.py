@@ -22,6 +22,23 @@ def host_threads():
     return max(1, min(16, len(os.sched_getaffinity(0))))
 
 
+def kernels_run(fn):
+    """Names of the kernels that fn launches, each with its device time in
+    microseconds (a kernel that returns at once is among them)."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    fn()
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as p:
+        fn()
+        torch.cuda.synchronize()
+    out = {}
+    for e in p.events():
+        if e.device_type == torch.autograd.DeviceType.CUDA:
+            out[e.name] = out.get(e.name, 0.0) + e.device_time
+    return out
+
+
 def oracle_problem(pb, jobs=None, finish_jobs=()):
     """Oracle results for the selected jobs (all when jobs is None) of a
     shared-trace Problem: dict job -> (served, digest, finish or None)."""

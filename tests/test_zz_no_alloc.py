@@ -3,9 +3,10 @@ outputs equal those of as_simulate_placements bit for bit (served counts,
 attainment, digests, every per-request output row) on calls in a row whose
 inputs shrink, so that the shared scratch array carries the previous call's
 contents into the next; on the speculative kernels (forced, with several
-segments), on the default path choice, and on re-runs that give up; and a
-call whose workspace would exceed the scratch is refused with AS_E_LIMITS
-before anything is launched."""
+segments, and on a trace cut into fewer segments so that they fit the
+scratch), on the default path choice, and on re-runs that give up; and a call
+whose workspace exceeds the scratch however it is cut is refused with
+AS_E_LIMITS before anything is launched."""
 import os
 import sys
 
@@ -13,7 +14,7 @@ import numpy as np
 import pytest
 
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
-from gpu_common import say  # noqa: E402
+from gpu_common import kernels_run, say  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -78,6 +79,21 @@ def test_noalloc_equals_allocating_entry_point_default_path(sim, monkeypatch):
     for k, pb in enumerate(_problems()[:2]):
         say(f"noalloc default path: call {k}, {pb.n_jobs} jobs x {len(pb.t)} requests")
         _same(_run(sim, pb, True), _run(sim, pb, False), f"default path call {k}")
+
+
+@pytest.mark.parametrize("path", ["", "spec"])
+def test_noalloc_cuts_the_trace_to_fit_the_scratch(sim, monkeypatch, path):
+    """1024 jobs x 900,000 requests need 0.3 GB of workspace with as many
+    segments as fill the device, and fit the 256 MiB scratch with fewer: the
+    speculative kernels take the call, by default and where they are forced."""
+    for v in ("ALPASERVE_SPEC_SEGMENTS", "ALPASERVE_SPEC_WARMUP", "ALPASERVE_SPEC_CAP", "ALPASERVE_SPEC_CKPT"):
+        monkeypatch.delenv(v, raising=False)
+    monkeypatch.setenv("ALPASERVE_PATH", path)
+    pb = _problems()[0]
+    say(f"noalloc cut to fit: path {path!r}, {pb.n_jobs} jobs x {len(pb.t)} requests")
+    names = kernels_run(lambda: _run(sim, pb, True))
+    assert any("spec_pass0" in n for n in names), sorted(names)
+    _same(_run(sim, pb, True), _run(sim, pb, False), f"cut to fit {path!r}")
 
 
 def test_noalloc_equals_allocating_entry_point_give_up(sim, monkeypatch):
