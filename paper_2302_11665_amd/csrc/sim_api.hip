@@ -148,6 +148,23 @@ bool lean_takes(const KArgs& a, int smax, int chunk = 2048) {
   return records + (size_t)a.M * pow2ceil(a.C) * smax * 8 + (size_t)chunk * 20 <= shared_lds_limit();
 }
 
+// Jobs with trace segments of their own: whether each gets a wavefront (the
+// group-per-lane kernel) or the general kernel packs 64 / W of them into one.
+// A wavefront to itself has the shorter chain, by two to nine times while the
+// SIMDs are not full; packed, a request of all of them costs one wavefront
+// about what two to four requests cost there.  The line lies at the jobs per
+// SIMD where both take the same time on segments of equal length (which the
+// host does not know; with lengths spread over a factor of ten the packed
+// wavefronts wait for their longest and lose up to three times there).
+// Measured, packed / one per wavefront, at jobs per SIMD: 1 lane 1.5 at 16 and
+// 0.6 at 64; 2 lanes 0.9 to 1.2 at 16, 0.5 to 0.7 at 32; 4 lanes 1.7 at 2, 0.9
+// at 4, 0.4 at 16; 8 lanes 1.2 at 2 and 0.8 at 3; 16 lanes 1.0 and 0.7 to 0.8;
+// 32 lanes 1.1 to 1.3 and 0.7 to 1.1, 0.6 at 4.
+bool seg_one_per_wave(int W, int64_t J) {
+  const int64_t per_simd = W >= 64 ? INT64_MAX / 65536 : W >= 8 ? 2 : W == 4 ? 4 : W == 2 ? 16 : 24;
+  return J <= per_simd * simd_count();
+}
+
 // Lanes per job W and groups per lane GPL (W * GPL >= G, powers of two).
 // Cost model: a wavefront issues in order, so the time of a launch is about
 // (wavefronts per SIMD, at least 1) x (instructions per request of one
@@ -693,12 +710,12 @@ int as_simulate_jobs(const double* t, const int32_t* model, const int64_t* seg_o
   a.out_digest = out_digest;
   a.finish_stride = finish_stride;
   hipStream_t s = (hipStream_t)stream;
-  // one job per wavefront (the requests of a wavefront are one job's)
   const int Ws = pow2ceil(a.G);
   const size_t lds_seg = as_dev::lean_lds_bytes(Ws, a.M, pow2ceil(a.C), smax, false, as_dev::kWaves);
   int GPL = 1;
   const bool general = choose_shape(a.G, n_jobs, true, a.M, a.C, smax, W, GPL);
-  if (use_shared_path() && (general || (Ws == 64 && lean_takes(a, smax, 1024))) && lds_seg <= shared_lds_limit()) {
+  if (use_shared_path() && (general || (Ws == 64 && lean_takes(a, smax, 1024))) && lds_seg <= shared_lds_limit() &&
+      seg_one_per_wave(Ws, n_jobs)) {
     hipError_t e = hipSuccess;
     const int64_t n_rows = finish_stride > 0 ? a.n_finish : 0;
     // Jobs longest first.  With more jobs than seg_waves_per_simd()

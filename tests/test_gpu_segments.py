@@ -1,7 +1,7 @@
 """GPU parity of the segmented entry point (as_simulate_jobs): jobs that each
 bring their own trace segment and SLO scale, against the oracle job by job,
-bit-exact.  Covers both kernels behind it (up to 32 groups: the general
-kernel; more: one job per wavefront), empty segments, job records naming a
+bit-exact.  Covers both kernels behind it (one job per wavefront, and many jobs
+on up to 32 groups packed into fewer wavefronts), empty segments, job records naming a
 missing placement or segment (empty jobs), scales 0 and +inf, and output rows
 whose stride is shorter or longer than the segments."""
 import os
@@ -11,7 +11,7 @@ import numpy as np
 import pytest
 
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
-from gpu_common import say  # noqa: E402
+from gpu_common import kernels_run, say  # noqa: E402
 
 import oracle  # noqa: E402
 
@@ -188,3 +188,33 @@ def test_job_queue_matches_one_job_per_wavefront(dev, monkeypatch, J, blocks):
     sub = dict(c, jp=c["jp"][sample], js=c["js"][sample], jsc=c["jsc"][sample])
     fin_sub = [sample.index(j) for j in finish]
     _check(sub, tuple(np.asarray(x)[sample] for x in got[:3]) + (got[3],), fin_sub, stride)
+
+
+@pytest.mark.parametrize("G,per_simd,over", [(1, 24, 0), (1, 24, 1), (2, 16, 0), (2, 16, 1), (3, 4, 0), (3, 4, 1),
+                                             (8, 2, 1), (16, 2, 0), (16, 2, 1), (32, 2, 0), (32, 2, 1), (33, 5, 0)])
+def test_many_jobs_are_packed(dev, G, per_simd, over):
+    """Up to per_simd jobs per SIMD run one per wavefront; one job more, and the
+    general kernel packs 64 / W of them into a wavefront (never beyond 32
+    groups).  Either way the outputs are the oracle's, rows included, and both
+    kernels agree on the jobs that they have in common."""
+    import torch
+    J = per_simd * 4 * torch.cuda.get_device_properties(0).multi_processor_count + over
+    rng = np.random.default_rng(1500 + G)
+    c = _case(rng, G, 4)
+    n_seg = len(c["offs"]) - 1
+    c = dict(c, jp=rng.integers(0, c["gcfg"].shape[0], J).astype(np.int32),
+             js=rng.integers(0, n_seg, J).astype(np.int32), jsc=rng.choice([0.5, 2.0, 5.0, np.inf], J))
+    finish = [0, J // 2, J - 1]
+    stride = 500
+    say("packed jobs", G, "groups", J, "jobs")
+    names = kernels_run(lambda: _run(dev, c, finish, stride))
+    assert any("sim_kernel" in n for n in names) == bool(over), sorted(names)
+    assert any("seg_kernel" in n for n in names) == (not over), sorted(names)
+    got = _run(dev, c, finish, stride)
+    sample = sorted(set(rng.choice(J, size=24, replace=False).tolist()) | set(finish))
+    sub = dict(c, jp=c["jp"][sample], js=c["js"][sample], jsc=c["jsc"][sample])
+    fin_sub = [sample.index(j) for j in finish]
+    _check(sub, tuple(np.asarray(x)[sample] for x in got[:3]) + (got[3],), fin_sub, stride)
+    few = dict(c, jp=c["jp"][:200], js=c["js"][:200], jsc=c["jsc"][:200])  # one per wavefront on any group count
+    for a, b in zip(_run(dev, few, [], 0)[:3], got[:3]):
+        assert np.array_equal(np.asarray(a), np.asarray(b)[:200])
