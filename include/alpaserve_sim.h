@@ -159,10 +159,11 @@ typedef struct {
  *                    finish_jobs[f]'s outputs for requests i < min(segment
  *                    length, finish_stride)
  * Asynchronous on `stream`.  Many jobs on up to 32 groups are packed several to
- * a wavefront; otherwise a job has a wavefront to itself.  Then 2..4096 jobs are
- * sorted by segment length on the device: up to two wavefronts per SIMD they
- * run one per wavefront, longest and shortest segment alternating; beyond, two
- * wavefronts per SIMD take them in turn, longest first, from a counter.
+ * a wavefront; otherwise a job has a wavefront to itself.  Then more jobs than
+ * SIMDs, up to 4096, are sorted by segment length on the device: up to two
+ * wavefronts per SIMD they run one per wavefront, longest and shortest segment
+ * alternating; beyond, two wavefronts per SIMD take them in turn, longest first,
+ * from a counter.
  * Neither changes any result.  The order array and the counter (4 bytes per
  * job, plus 4) come from the library's memory pool and are released
  * stream-ordered.

@@ -136,12 +136,12 @@ def _permuted(c, perm):
     return dict(c, jp=c["jp"][perm], js=c["js"][perm], jsc=c["jsc"][perm])
 
 
-@pytest.mark.parametrize("J", [2, 300, 4096, 4100])
+@pytest.mark.parametrize("J", [2, 300, 1500, 4096, 4100])
 def test_launch_order_does_not_change_results(dev, J):
     """With more than 32 groups the jobs run one per wavefront, launched
-    longest and shortest segment alternating (sorted on the device for up
-    to 4096 jobs, in the given order beyond): the results, indexed by job,
-    are the same for any order of the job records."""
+    longest and shortest segment alternating (sorted on the device from more
+    jobs than SIMDs up to 4096, in the given order otherwise): the results,
+    indexed by job, are the same for any order of the job records."""
     rng = np.random.default_rng(900 + J)
     c = _case(rng, 64, 2)
     n_seg = len(c["offs"]) - 1
@@ -157,6 +157,18 @@ def test_launch_order_does_not_change_results(dev, J):
     sample = sorted(set(rng.choice(J, size=min(J, 24), replace=False).tolist()))
     sub = dict(c, jp=c["jp"][sample], js=c["js"][sample], jsc=c["jsc"][sample])
     _check(sub, tuple(np.asarray(x)[sample] for x in ref[:3]) + (None,), [], 0)
+
+
+def test_no_sort_where_every_job_has_a_simd(dev):
+    """Jobs that have a SIMD each need no launch order: the call is one kernel."""
+    import torch
+    simds = 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    c = _case(np.random.default_rng(77), 4, 1)
+    for J, sorts in ((8, False), (simds, False), (simds + 1, True)):
+        cj = dict(c, jp=np.zeros(J, np.int32), js=np.zeros(J, np.int32), jsc=np.ones(J))
+        names = kernels_run(lambda: _run(dev, cj, [], 0))
+        say("sort", J, sorts)
+        assert any("seg_order" in n for n in names) == sorts, sorted(names)
 
 
 @pytest.mark.parametrize("J,blocks", [(13, 3), (300, 1), (1000, 3), (4096, 7)])
