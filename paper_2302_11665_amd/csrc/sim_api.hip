@@ -135,8 +135,20 @@ int lean_waves_per_block(int64_t waves, int W, const KArgs& a, int smax, bool st
   return w;
 }
 
-// Wavefronts of J jobs (K scales per placement) at jw jobs per wavefront.
+// Wavefronts of J jobs (K scales per placement) at jw jobs of one scale per
+// wavefront.
 int64_t lean_wave_count(int64_t J, int64_t K, int jw) { return K * ((J / K + jw - 1) / jw); }
+
+// Whether wavefronts take jobs of several scales, which costs a request two
+// instructions: where wavefronts of one scale, at most one job for every
+// placement, are a tenth more and do not all have a SIMD of their own.  Measured
+// at 4000 requests, apart and mixed: 1 placement x 16,384 scales on 4 four-stage
+// groups 3.16 and 0.35 ms, on 32 one-stage groups 3.42 and 1.89; 3 x 4096 on 16
+// four-stage groups 1.04 and 0.84.
+bool lean_mixes_scales(int W, int64_t J, int64_t K, int jw) {
+  const int64_t apart = lean_wave_count(J, K, jw), mixed = (J + jw - 1) / jw;
+  return W < 64 && apart > simd_count() && mixed * 11 < apart * 10;
+}
 
 // Which calls the group-per-lane kernels take, by their stage-latency tables:
 // the sizes these calls have always been taken up to (the table, the model
@@ -431,14 +443,15 @@ int run_shared_multi(const KArgs& a, void* dev_args, const ShapeJobs* sh, int n,
 int run_trace_kernels(KArgs& a, int W, int smax, hipStream_t stream, bool only_check) {
   const int64_t J = a.J;
   const int Ws = pow2ceil(a.G), jw = lean_jobs_per_wave(Ws, J);
+  const bool mixes = lean_mixes_scales(Ws, J, a.K, jw);
   // the jobs, and those with a per-request row once more
-  const int64_t nw = lean_wave_count(J, a.K, jw) + (a.n > 0 ? a.n_finish : 0);
+  const int64_t nw = (mixes ? (J + jw - 1) / jw : lean_wave_count(J, a.K, jw)) + (a.n > 0 ? a.n_finish : 0);
   const int waves = lean_waves_per_block(nw, Ws, a, smax, false);
   const size_t lds_shared = as_dev::lean_lds_bytes(Ws, a.M, pow2ceil(a.C), smax, false, waves);
   if (use_shared_path() && lean_takes(a, smax) && lds_shared <= shared_lds_limit()) {
     if (only_check) return AS_OK;
-    const hipError_t e = launch_lean_any(LeanKind::kShared, Ws, smax, a, jw, (nw + waves - 1) / waves, waves,
-                                         lds_shared, stream);
+    const hipError_t e = launch_lean_any(mixes ? LeanKind::kScales : LeanKind::kShared, Ws, smax, a, jw,
+                                         (nw + waves - 1) / waves, waves, lds_shared, stream);
     if (e != hipSuccess) return fail(AS_E_HIP, "kernel launch failed: %s", hipGetErrorString(e));
     return ok();
   }

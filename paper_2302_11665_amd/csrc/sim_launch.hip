@@ -41,10 +41,13 @@ void lean_t(LeanKind kind, const KArgs& a, int jw, int64_t blocks, int waves, si
   const dim3 grid((unsigned)blocks), block(64 * (unsigned)waves);
   switch (kind) {
     case LeanKind::kShared:
-      hipLaunchKernelGGL((as_dev::shared_kernel<AS_W, SMAX, false>), grid, block, lds, s, a, jw);
+      hipLaunchKernelGGL((as_dev::shared_kernel<AS_W, SMAX, false, false>), grid, block, lds, s, a, jw);
+      break;
+    case LeanKind::kScales:  // (64 lanes hold one job)
+      hipLaunchKernelGGL((as_dev::shared_kernel<AS_W, SMAX, false, AS_W < 64>), grid, block, lds, s, a, jw);
       break;
     case LeanKind::kStats:
-      hipLaunchKernelGGL((as_dev::shared_kernel<AS_W, SMAX, true>), grid, block, lds, s, a, jw);
+      hipLaunchKernelGGL((as_dev::shared_kernel<AS_W, SMAX, true, false>), grid, block, lds, s, a, jw);
       break;
     default: hipLaunchKernelGGL((as_dev::seg_kernel<AS_W, SMAX>), grid, block, lds, s, a); break;
   }

@@ -20,10 +20,11 @@ template <int W>
 hipError_t launch_lds(int gpl, int smax, bool seg, const KArgs& a, size_t lds, hipStream_t s);
 
 // Group-per-lane kernels (sim_lean.hpp), one group per lane: the jobs of a
-// shared trace, the same with the heuristic's statistics (one SLO scale), or
-// segmented jobs (a.order, a.next_slot).  jw: jobs per wavefront of a shared
-// trace; blocks workgroups of `waves` wavefronts.
-enum class LeanKind { kShared, kStats, kSeg };
+// shared trace (one scale, or several scales, a wavefront), the same with the
+// heuristic's statistics (one scale), or segmented jobs (a.order, a.next_slot).
+// jw: jobs per wavefront of a shared trace; blocks workgroups of `waves`
+// wavefronts.
+enum class LeanKind { kShared, kScales, kStats, kSeg };
 template <int W>
 hipError_t launch_lean(LeanKind kind, int smax, const KArgs& a, int jw, int64_t blocks, int waves, size_t lds,
                        hipStream_t s);

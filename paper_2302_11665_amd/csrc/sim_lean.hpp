@@ -55,6 +55,7 @@ struct LeanLane {
   double F[SMAX];
   uint64_t fin;  // bit patterns of this group's accepted finish times, summed
   double busy;   // statistics: this group's busy time
+  double sigma;  // MS: this job's SLO scale
 };
 
 // Dispatch and admission on the exec mask, then the commit under it: lanes
@@ -211,7 +212,9 @@ __device__ __forceinline__ double lean_min(double v) {
   return v;
 }
 
-template <int W, int SMAX, int BIT, bool STATS, bool ROW>
+// MS: the jobs of the wavefront differ in scale, and q.dl is the model's
+// d_single (two more instructions a request).
+template <int W, int SMAX, int BIT, bool STATS, bool ROW, bool MS>
 __device__ __forceinline__ void lean_step(LeanLane<SMAX>& st, const LeanReq<SMAX>& q, uint32_t blo, uint32_t bhi,
                                           uint32_t& sr, uint32_t orow) {
   const bool host = __builtin_amdgcn_inverse_ballot_w64(lean_uniform(q.hm));
@@ -221,28 +224,29 @@ __device__ __forceinline__ void lean_step(LeanLane<SMAX>& st, const LeanReq<SMAX
 #pragma unroll
   for (int s = 0; s < SMAX; ++s) f = fs[s] = vmax(f, st.F[s]) + q.L[s];
   const double slow = STATS ? lean_slow<SMAX>(q.L) : 0.0;
-  lean_commit<SMAX, BIT, STATS, ROW>(st, mn, key, blo, bhi, fs, q.dl, slow, sr, orow);
+  const double dl = MS ? q.t + st.sigma * q.dl : q.dl;
+  lean_commit<SMAX, BIT, STATS, ROW>(st, mn, key, blo, bhi, fs, dl, slow, sr, orow);
 }
 
-template <int W, int SMAX, bool STATS, bool ROW, int K>
+template <int W, int SMAX, bool STATS, bool ROW, bool MS, int K>
 __device__ __forceinline__ void lean_steps(LeanLane<SMAX>& st, const LeanReq<SMAX> (&q)[kLeanB], uint32_t blo,
                                            uint32_t bhi, uint32_t& sr, uint32_t orow) {
   if constexpr (K < kLeanB) {
-    lean_step<W, SMAX, K, STATS, ROW>(st, q[K], blo, bhi, sr, orow);
-    lean_steps<W, SMAX, STATS, ROW, K + 1>(st, q, blo, bhi, sr, orow);
+    lean_step<W, SMAX, K, STATS, ROW, MS>(st, q[K], blo, bhi, sr, orow);
+    lean_steps<W, SMAX, STATS, ROW, MS, K + 1>(st, q, blo, bhi, sr, orow);
   }
 }
 
 // kLeanB staged requests.  Returns their accept bits (bit k: request k was
 // accepted by this lane).
-template <int W, int SMAX, bool UNI, bool STATS, bool ROW>
+template <int W, int SMAX, bool UNI, bool STATS, bool ROW, bool MS>
 __device__ __forceinline__ uint32_t lean_batch(LeanLane<SMAX>& st, const unsigned char* r, const char* lrow,
                                                uint32_t blo, uint32_t bhi, uint32_t orow) {
   uint32_t sr = 0;
   LeanReq<SMAX> q[kLeanB];
 #pragma unroll
   for (int k = 0; k < kLeanB; ++k) q[k] = lean_read<SMAX, UNI>(r + k * lean_stride(SMAX), lrow);
-  lean_steps<W, SMAX, STATS, ROW, 0>(st, q, blo, bhi, sr, orow);
+  lean_steps<W, SMAX, STATS, ROW, MS, 0>(st, q, blo, bhi, sr, orow);
   return sr;
 }
 
@@ -253,8 +257,8 @@ __device__ __forceinline__ void lean_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// What one wavefront simulates: jw <= 64 / W jobs of one trace at one SLO
-// scale (every member but cfg and hm is the same in all lanes).
+// What one wavefront simulates: jw <= 64 / W jobs of one trace (every member but
+// cfg, hm and, with MS, sigma is the same in all lanes).
 struct LeanIn {
   const double* t;
   const int32_t* model;
@@ -282,7 +286,7 @@ struct LeanWave {
   const char* urow;  // the first group's (UNI: every group's)
   int lshift;        // a model's rows are 1 << lshift bytes apart
   unsigned char* rec;  // lean_wave_bytes of LDS, then finish times by rank (ROW)
-  double slo;          // lane m: model m's SLO
+  double slo;          // lane m: model m's SLO (MS: its d_single)
   uint64_t hm;         // lane m: lanes whose group hosts model m
   uint64_t hosted;     // models some job hosts
   uint32_t blo, bhi;   // this lane's job's lanes below it
@@ -290,7 +294,7 @@ struct LeanWave {
 
 // sL: stage-latency table [M][Cp][SMAX] in LDS; cfg: this lane's group's
 // configuration, -1: no group.
-template <int W, int SMAX, class Args>
+template <int W, int SMAX, bool MS = false, class Args>
 __device__ __forceinline__ LeanWave<W, SMAX> lean_wave(const Args& a, double sigma, int cfg, uint64_t hm,
                                                        const double* sL, int lshift, unsigned char* rec) {
   LeanWave<W, SMAX> w;
@@ -302,7 +306,7 @@ __device__ __forceinline__ LeanWave<W, SMAX> lean_wave(const Args& a, double sig
       sL + (valid ? __builtin_amdgcn_readlane(c, __builtin_ctzll(valid)) : 0) * SMAX);
   w.lshift = lshift;
   w.rec = rec;
-  w.slo = lane < a.M ? sigma * a.d_single[lane] : 0.0;
+  w.slo = lane < a.M ? (MS ? a.d_single[lane] : sigma * a.d_single[lane]) : 0.0;
   w.hm = hm;
   w.hosted = __builtin_amdgcn_ballot_w64(hm != 0);
   const uint64_t below = ((1ull << lane) - 1) & ~((1ull << (lane / W * W)) - 1);
@@ -323,7 +327,7 @@ __device__ __forceinline__ bool lean_uni(int cfg) {
 // lanes, the request of rank k at bit k.  ROW: finish times (-1: rejected) by
 // rank are left behind the staged requests.  Called by whole wavefronts in
 // uniform control flow (the commit restores a full exec mask).
-template <int W, int SMAX, bool UNI, bool STATS, bool ROW>
+template <int W, int SMAX, bool UNI, bool STATS, bool ROW, bool MS = false>
 __device__ __forceinline__ uint64_t lean_chunk(LeanLane<SMAX>& st, const LeanWave<W, SMAX>& w, double tv, int mv,
                                                bool mine, int rank, int nh) {
   constexpr int R = lean_stride(SMAX);
@@ -342,7 +346,7 @@ __device__ __forceinline__ uint64_t lean_chunk(LeanLane<SMAX>& st, const LeanWav
   lean_fence();
   if (mine) {
     unsigned char* r = w.rec + rank * R;
-    *(double2*)r = make_double2(tv, tv + ms);  // the deadline t + SLO, each rounded once
+    *(double2*)r = make_double2(tv, MS ? ms : tv + ms);  // the deadline t + SLO, each rounded once
     const uint32_t off = (uint32_t)mv << w.lshift;
     if constexpr (UNI) {
       const double* l = reinterpret_cast<const double*>(w.urow + off);
@@ -368,7 +372,7 @@ __device__ __forceinline__ uint64_t lean_chunk(LeanLane<SMAX>& st, const LeanWav
   lean_fence();
   const int nb = (nh + kLeanB - 1) / kLeanB;
   for (int b = 0; b < nb; ++b) {
-    const uint32_t bits = lean_batch<W, SMAX, UNI, STATS, ROW>(st, w.rec + b * kLeanB * R, w.lrow, w.blo, w.bhi,
+    const uint32_t bits = lean_batch<W, SMAX, UNI, STATS, ROW, MS>(st, w.rec + b * kLeanB * R, w.lrow, w.blo, w.bhi,
                                                                olds + b * kLeanB * 8);
     word |= (uint64_t)bits << (b * kLeanB);
   }
@@ -387,16 +391,17 @@ __device__ __forceinline__ bool lean_mine(const LeanWave<W, SMAX>& w, bool in, i
 }
 
 // cnt: STATS, this wavefront's [jw][M] served counters in LDS, zeroed.
-template <int W, int SMAX, bool UNI, bool STATS, bool ROW>
+template <int W, int SMAX, bool UNI, bool STATS, bool ROW, bool MS>
 __device__ __forceinline__ LeanOut lean_run(const KArgs& a, const LeanIn& in, const double* sL, int lshift,
                                             unsigned char* rec, uint32_t* cnt) {
   const int lane = threadIdx.x & 63;
-  const LeanWave<W, SMAX> w = lean_wave<W, SMAX>(a, in.sigma, in.cfg, in.hm, sL, lshift, rec);
+  const LeanWave<W, SMAX> w = lean_wave<W, SMAX, MS>(a, in.sigma, in.cfg, in.hm, sL, lshift, rec);
   LeanLane<SMAX> st;
 #pragma unroll
   for (int s = 0; s < SMAX; ++s) st.F[s] = 0.0;
   st.fin = 0;
   st.busy = 0.0;
+  st.sigma = in.sigma;
   uint64_t hash = 0;
   int64_t served = 0;
   const int64_t n = in.n, top = n > 0 ? n - 1 : 0;
@@ -412,7 +417,7 @@ __device__ __forceinline__ LeanOut lean_run(const KArgs& a, const LeanIn& in, co
     mn = in.model[ahead < n ? ahead : top];
     int rank, nh;
     const bool mine = lean_mine<W, SMAX>(w, base + lane < n, mv, rank, nh);
-    uint64_t word = lean_chunk<W, SMAX, UNI, STATS, ROW>(st, w, tv, mv, mine, rank, nh);
+    uint64_t word = lean_chunk<W, SMAX, UNI, STATS, ROW, MS>(st, w, tv, mv, mine, rank, nh);
     served += __builtin_popcountll(word);
     if (STATS || (in.digest && nh < 64)) {
       // back to trace order: lane e is request e, whose bit is at its rank
@@ -466,20 +471,22 @@ __device__ __forceinline__ int lean_table(const Args& a, double* sL, size_t& byt
   return lshift;
 }
 
-template <int W, int SMAX, bool STATS, bool ROW>
+template <int W, int SMAX, bool STATS, bool ROW, bool MS = false>
 __device__ __forceinline__ LeanOut lean_go(const KArgs& a, const LeanIn& in, const double* sL, int lshift,
                                            unsigned char* rec, uint32_t* cnt) {
   if (lean_uni(in.cfg))
-    return lean_run<W, SMAX, true, STATS, ROW>(a, in, sL, lshift, rec, cnt);
-  return lean_run<W, SMAX, false, STATS, ROW>(a, in, sL, lshift, rec, cnt);
+    return lean_run<W, SMAX, true, STATS, ROW, MS>(a, in, sL, lshift, rec, cnt);
+  return lean_run<W, SMAX, false, STATS, ROW, MS>(a, in, sL, lshift, rec, cnt);
 }
 
 // Workgroup blk of the jobs v of one shared trace.  Wavefront w runs jw
-// placements at one scale; after the last of them, wavefront by wavefront,
-// the jobs with a per-request row once more for the row alone (so that no
-// other job waits for the row's code).
-template <int W, int SMAX, bool STATS, bool ROWS>
+// placements at one scale or, with MS, jw jobs in a row whatever their scale;
+// after the last of them, wavefront by wavefront, the jobs with a per-request
+// row once more for the row alone (so that no other job waits for the row's
+// code).
+template <int W, int SMAX, bool STATS, bool ROWS, bool MS = false>
 __device__ __forceinline__ void lean_body(const KArgs& a, const JobSet& v, int64_t blk) {
+  static_assert(!(STATS && MS), "statistics launches run one scale a wavefront");
   extern __shared__ __align__(16) unsigned char smem[];
   double* sL = reinterpret_cast<double*>(smem);
   size_t tab = 0;
@@ -489,7 +496,8 @@ __device__ __forceinline__ void lean_body(const KArgs& a, const JobSet& v, int64
   unsigned char* rec = smem + tab + (size_t)wave * lean_wave_lds(W, a.M, SMAX, STATS);
   uint32_t* cnt = reinterpret_cast<uint32_t*>(rec + lean_wave_bytes(SMAX) + (64 + kLeanB) * 8);
   const int64_t w = blk * (int64_t)(blockDim.x >> 6) + wave;
-  const int64_t P = v.J / a.K, per = (P + v.jw - 1) / v.jw, nw = per * a.K;
+  const int64_t P = v.J / a.K, per = (P + v.jw - 1) / v.jw;
+  const int64_t nw = MS ? (v.J + v.jw - 1) / v.jw : per * a.K;
   const bool rows = ROWS && w >= nw;
   if (rows ? w - nw >= a.n_finish : w >= nw) return;
 
@@ -499,31 +507,42 @@ __device__ __forceinline__ void lean_body(const KArgs& a, const JobSet& v, int64
   in.n = a.n;
   in.row = nullptr;
   in.row_n = a.n;
-  int64_t p0, k;
+  // the jobs of the wavefront: slot s has job job0 + s * step
+  int64_t job0, step = a.K;
   if (rows) {
-    const int job = a.finish_jobs[w - nw];
-    p0 = job / a.K;
-    k = job % a.K;
+    job0 = a.finish_jobs[w - nw];
     in.jw = 1;
     in.row = a.out_finish + (w - nw) * a.n;
+  } else if (MS) {
+    job0 = w * v.jw;
+    step = 1;
+    in.jw = (int)(v.J - job0 < v.jw ? v.J - job0 : v.jw);
   } else {
-    k = w / per;
-    p0 = (w % per) * v.jw;
+    const int64_t k = w / per, p0 = (w % per) * v.jw;
+    job0 = p0 * a.K + k;
     in.jw = (int)(P - p0 < v.jw ? P - p0 : v.jw);
   }
-  in.sigma = a.slo_scale[k];
   in.digest = !rows && v.out_digest != nullptr;
   const int slot = lane / W, g = lane % W;
   const bool mine = slot < in.jw && g < v.G;
-  in.cfg = mine ? v.group_cfg[(p0 + slot) * v.G + g] : -1;
+  const int64_t job = job0 + slot * step;
+  // (a placement's number: J < 2^31)
+  const int64_t p = MS ? (int64_t)((uint32_t)(slot < in.jw ? job : job0) / (uint32_t)a.K) : job0 / a.K + slot;
+  in.sigma = a.slo_scale[MS ? (slot < in.jw ? job : job0) - p * a.K : job0 % a.K];
+  in.cfg = mine ? v.group_cfg[p * v.G + g] : -1;
   if (in.cfg >= a.C || in.cfg < 0) in.cfg = -1;
   const uint64_t valid = __builtin_amdgcn_ballot_w64(in.cfg >= 0);
   in.hm = 0;
   const uint64_t groups = W == 64 ? ~0ull : (1ull << W) - 1;
+  int64_t pj = job0 / a.K, kj = job0 % a.K;
 #pragma unroll 4
   for (int j = 0; j < in.jw; ++j) {
-    const uint64_t x = lane < a.M ? v.host_mask[(p0 + j) * a.M + lane] & groups : 0;
+    const uint64_t x = lane < a.M ? v.host_mask[pj * a.M + lane] & groups : 0;
     in.hm |= x << (W == 64 ? 0 : j * W);
+    if (!MS || ++kj == a.K) {
+      ++pj;
+      kj = 0;
+    }
   }
   in.hm &= valid;
   if constexpr (STATS) {
@@ -534,8 +553,7 @@ __device__ __forceinline__ void lean_body(const KArgs& a, const JobSet& v, int64
     if constexpr (ROWS) (void)lean_go<W, SMAX, false, true>(a, in, sL, lshift, rec, cnt);
     return;
   }
-  const LeanOut o = lean_go<W, SMAX, STATS, false>(a, in, sL, lshift, rec, cnt);
-  const int64_t job = (p0 + slot) * a.K + k;
+  const LeanOut o = lean_go<W, SMAX, STATS, false, MS>(a, in, sL, lshift, rec, cnt);
   if (slot < in.jw && g == 0) {
     v.out_served[job] = o.served;
     if (v.out_attain) v.out_attain[job] = a.n > 0 ? (double)o.served / (double)a.n : 0.0;
@@ -549,14 +567,14 @@ __device__ __forceinline__ void lean_body(const KArgs& a, const JobSet& v, int64
     lean_fence();
     if (v.out_model_served)
       for (int i = lane; i < in.jw * a.M; i += 64)
-        v.out_model_served[((p0 + i / a.M) * a.K + k) * a.M + i % a.M] = (int64_t)cnt[i];
+        v.out_model_served[(job0 + i / a.M * step) * a.M + i % a.M] = (int64_t)cnt[i];
   }
 }
 
-template <int W, int SMAX, bool STATS>
+template <int W, int SMAX, bool STATS, bool MS>
 __global__ __launch_bounds__(kThreads) void shared_kernel(const KArgs a, int jw) {
   if (a.gate && *a.gate == 0) return;
-  lean_body<W, SMAX, STATS, !STATS>(a, job_set(a, jw), blockIdx.x);
+  lean_body<W, SMAX, STATS, !STATS, MS>(a, job_set(a, jw), blockIdx.x);
 }
 
 // Jobs with trace segments of their own, one per wavefront at a time: slot ->

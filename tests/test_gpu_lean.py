@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_common import compare, oracle_problem, say
+from gpu_common import compare, kernels_run, oracle_problem, say
 
 pytestmark = pytest.mark.gpu
 
@@ -73,6 +73,24 @@ def test_several_jobs_per_wavefront(api, G, P):
     """More jobs than SIMDs: several per wavefront, the last wavefront part empty."""
     pb = _problem(P, 150, G, P, [3.0])
     _check(api, pb, f"G={G} P={P}", sorted({*range(0, P, 41), *range(P - 70, P), *pb.finish_jobs.tolist()}))
+
+
+@pytest.mark.parametrize("G,P,per_simd,mixes", [
+    (1, 1, 1.01, True), (1, 5, 2.3, False), (4, 1, 3.1, True), (4, 3, 3.2, True), (6, 2, 4.5, True), (12, 1, 9.0, True),
+    (16, 7, 5.0, True), (32, 1, 1.5, True), (32, 2, 3.0, False), (33, 1, 1.2, False)])
+def test_many_scales_on_few_placements(api, G, P, per_simd, mixes):
+    """Few placements at many SLO scales: wavefronts of one scale would hold one
+    job a placement, so they take jobs of several scales (never 64 lanes, which
+    hold one job, nor where a placement's jobs fill the wavefronts anyway)."""
+    import torch
+    K = int(per_simd * 4 * torch.cuda.get_device_properties(0).multi_processor_count) // P
+    scales = np.geomspace(0.2, 30.0, K)
+    scales[K // 3], scales[K // 2] = 0.0, np.inf
+    pb = _problem(G * 10 + P, 137, G, P, scales.tolist())
+    names = kernels_run(lambda: api.simulate_problem(pb))
+    assert any("shared_kernel" in n and n.count("true") == 1 for n in names) == mixes, sorted(names)
+    _check(api, pb, f"G={G} P={P} K={K}", sorted({*range(0, P * K, 7), *range(P * K - 70, P * K), K // 3, K // 2,
+                                                  *pb.finish_jobs.tolist()}))
 
 
 def test_infinite_finish_times(api):
