@@ -112,7 +112,9 @@ __device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
 // DPP controls: quad_perm [1,0,3,2] (lane ^ 1), quad_perm [2,3,0,1] (lane ^ 2),
 // row_half_mirror (i <-> 7 - i within 8 lanes), row_mirror (i <-> 15 - i
 // within 16 lanes).  Applied in this order each doubles the span reduced.
-constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
+// row_bcast:15 (a row's last lane to all of the next row), row_bcast:31 (lane
+// 31 to the upper two rows).
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140, kBcast15 = 0x142, kBcast31 = 0x143;
 
 // Min over each aligned group of W lanes, result in every lane of the group.
 template <int W>

@@ -23,10 +23,13 @@
 //     is plain moves under it, with no selects.
 // Measured, nanoseconds per request of a lone wavefront, before (records,
 // branches on ties and single hosts, selects) and now: 16 lanes per job and 4
-// stages 154 and 90, 4 lanes and 4 stages 151 and 79, 64 lanes and 1 stage 154
-// and 108, 64 lanes and 4 stages 178 and 121.  With two wavefronts on every
-// SIMD the first takes 141 (was 185); with eight, 64 lanes and 1 stage 534 (was
-// 525): there the instructions count, and about as many replace the old ones.
+// stages 154 and 91, 4 lanes and 4 stages 151 and 79, 64 lanes and 1 stage 156
+// and 104, 64 lanes and 4 stages 181 and 118.  With two wavefronts on every
+// SIMD the first takes 141 (was 185).  With eight the vector instructions count,
+// which is why a wavefront of one job ends its minimum in a lane read and breaks
+// ties on the scalar unit: 64 lanes and 1 stage, 8192 jobs of 3000 requests,
+// take 1.44 ms with that, 1.72 with swaps and vector masks, 1.66 with the
+// branches; 6000 jobs of 20,000 requests of their own 6.8, 8.2 and 6.7 ms.
 //
 // Exactness: v_max_f64, single v_add_f64, no FMA, in the definition's order,
 // so finish times are bit-identical to a sequential IEEE evaluation.
@@ -64,24 +67,61 @@ struct LeanLane {
 // deadline take the projected state.  Lane and DPP reads of
 // vector registers written here, and of lanes after the exec mask's vector
 // writes, are at least four instructions away.
+#define AS_LEAN_TAIL                             \
+  "v_cmpx_ngt_f64_e32 vcc, %[f], %[dl]\n\t"      \
+  "v_mov_b64_e32 %[F0], %[f0]\n\t"
+#define AS_LEAN_SUMS                             \
+  "v_lshl_add_u64 %[fin], %[f], 0, %[fin]\n\t"   \
+  "v_or_b32_e32 %[sr], %[bit], %[sr]\n\t"
+#define AS_LEAN_END "s_mov_b64 exec, -1"
+#define AS_LEAN_END1 "s_mov_b64 exec, -1\n\ts_nop 0"  // one stage: the fifth instruction
+#define AS_LEAN_OUT AS_LEAN_TMP, [fin] "+v"(st.fin), [sr] "+v"(sr), [F0] "+v"(st.F[0])
+#define AS_LEAN_IN AS_LEAN_SEL, [key] "v"(key), [f] "v"(f), [dl] "v"(dl), [f0] "v"(fs[0]), [bit] "i"(1 << BIT)
+#define AS_LEAN_ASM(MOVS, OUTS, INS, END)                                                                     \
+  if constexpr (STATS)                                                                                        \
+    asm(AS_LEAN_HEAD AS_LEAN_TAIL MOVS AS_LEAN_SUMS "v_add_f64 %[busy], %[busy], %[slow]\n\t" END             \
+        : AS_LEAN_OUT OUTS, [busy] "+v"(st.busy)                                                              \
+        : AS_LEAN_IN INS, [slow] "v"(slow)                                                                    \
+        : AS_LEAN_CLOBBERS);                                                                                  \
+  else if constexpr (ROW)                                                                                     \
+    asm volatile(AS_LEAN_HEAD AS_LEAN_TAIL MOVS AS_LEAN_SUMS "ds_write_b64 %[orow], %[f] offset:%[at]\n\t" END \
+                 : AS_LEAN_OUT OUTS                                                                           \
+                 : AS_LEAN_IN INS, [orow] "v"(orow), [at] "i"(8 * BIT)                                        \
+                 : AS_LEAN_CLOBBERS, "memory");                                                               \
+  else                                                                                                        \
+    asm(AS_LEAN_HEAD AS_LEAN_TAIL MOVS AS_LEAN_SUMS END : AS_LEAN_OUT OUTS : AS_LEAN_IN INS : AS_LEAN_CLOBBERS)
+#define AS_COMMA ,
+#define AS_LEAN_STAGES                                                                                          \
+  if constexpr (SMAX == 1) {                                                                                    \
+    AS_LEAN_ASM("", , , AS_LEAN_END1);                                                                          \
+  } else if constexpr (SMAX == 2) {                                                                             \
+    AS_LEAN_ASM("v_mov_b64_e32 %[F1], %[f1]\n\t", AS_COMMA[F1] "+v"(st.F[1]), AS_COMMA[f1] "v"(fs[1]),          \
+                AS_LEAN_END);                                                                                   \
+  } else if constexpr (SMAX == 4) {                                                                             \
+    AS_LEAN_ASM("v_mov_b64_e32 %[F1], %[f1]\n\tv_mov_b64_e32 %[F2], %[f2]\n\tv_mov_b64_e32 %[F3], %[f3]\n\t", \
+                AS_COMMA[F1] "+v"(st.F[1]) AS_COMMA[F2] "+v"(st.F[2]) AS_COMMA[F3] "+v"(st.F[3]),               \
+                AS_COMMA[f1] "v"(fs[1]) AS_COMMA[f2] "v"(fs[2]) AS_COMMA[f3] "v"(fs[3]), AS_LEAN_END);          \
+  } else {                                                                                                      \
+    AS_LEAN_ASM("v_mov_b64_e32 %[F1], %[f1]\n\tv_mov_b64_e32 %[F2], %[f2]\n\tv_mov_b64_e32 %[F3], %[f3]\n\t"  \
+                "v_mov_b64_e32 %[F4], %[f4]\n\tv_mov_b64_e32 %[F5], %[f5]\n\tv_mov_b64_e32 %[F6], %[f6]\n\t"  \
+                "v_mov_b64_e32 %[F7], %[f7]\n\t",                                                               \
+                AS_COMMA[F1] "+v"(st.F[1]) AS_COMMA[F2] "+v"(st.F[2]) AS_COMMA[F3] "+v"(st.F[3])                \
+                    AS_COMMA[F4] "+v"(st.F[4]) AS_COMMA[F5] "+v"(st.F[5]) AS_COMMA[F6] "+v"(st.F[6])            \
+                        AS_COMMA[F7] "+v"(st.F[7]),                                                             \
+                AS_COMMA[f1] "v"(fs[1]) AS_COMMA[f2] "v"(fs[2]) AS_COMMA[f3] "v"(fs[3]) AS_COMMA[f4] "v"(fs[4]) \
+                    AS_COMMA[f5] "v"(fs[5]) AS_COMMA[f6] "v"(fs[6]) AS_COMMA[f7] "v"(fs[7]),                    \
+                AS_LEAN_END);                                                                                   \
+  }
+
 #define AS_LEAN_HEAD                             \
   "v_cmpx_eq_f64_e32 vcc, %[mn], %[key]\n\t"     \
   "s_nop 1\n\t"                                  \
   "v_and_b32_e32 %[x], vcc_lo, %[blo]\n\t"       \
   "v_and_or_b32 %[x], vcc_hi, %[bhi], %[x]\n\t"  \
-  "v_cmpx_eq_u32_e32 vcc, 0, %[x]\n\t"           \
-  "v_cmpx_ngt_f64_e32 vcc, %[f], %[dl]\n\t"      \
-  "v_mov_b64_e32 %[F0], %[f0]\n\t"
-#define AS_LEAN_TAIL                             \
-  "v_lshl_add_u64 %[fin], %[f], 0, %[fin]\n\t"   \
-  "v_or_b32_e32 %[sr], %[bit], %[sr]\n\t"
-#define AS_LEAN_END "s_mov_b64 exec, -1"
-#define AS_LEAN_END1 "s_mov_b64 exec, -1\n\ts_nop 0"  // one stage: the fifth instruction
-#define AS_LEAN_OUT \
-  [x] "=&v"(x), [fin] "+v"(st.fin), [sr] "+v"(sr), [F0] "+v"(st.F[0])
-#define AS_LEAN_IN                                                                                           \
-  [mn] "v"(mn), [key] "v"(key), [blo] "v"(blo), [bhi] "v"(bhi), [f] "v"(f), [dl] "v"(dl), [f0] "v"(fs[0]), \
-      [bit] "i"(1 << BIT)
+  "v_cmpx_eq_u32_e32 vcc, 0, %[x]\n\t"
+#define AS_LEAN_TMP [x] "=&v"(x)
+#define AS_LEAN_SEL [mn] "v"(mn), [blo] "v"(blo), [bhi] "v"(bhi)
+#define AS_LEAN_CLOBBERS "vcc"
 // orow: LDS address where ROW stores the accepting lane's finish time, 8 bytes
 // per request of the batch.
 template <int SMAX, int BIT, bool STATS, bool ROW>
@@ -91,44 +131,42 @@ __device__ __forceinline__ void lean_commit(LeanLane<SMAX>& st, double mn, doubl
   static_assert(!(STATS && ROW), "statistics launches carry no rows");
   uint32_t x;
   const double f = fs[SMAX - 1];
-#define AS_LEAN_ASM(MOVS, OUTS, INS, END)                                                                     \
-  if constexpr (STATS)                                                                                        \
-    asm(AS_LEAN_HEAD MOVS AS_LEAN_TAIL "v_add_f64 %[busy], %[busy], %[slow]\n\t" END                          \
-        : AS_LEAN_OUT OUTS, [busy] "+v"(st.busy)                                                              \
-        : AS_LEAN_IN INS, [slow] "v"(slow)                                                                    \
-        : "vcc");                                                                                             \
-  else if constexpr (ROW)                                                                                     \
-    asm volatile(AS_LEAN_HEAD MOVS AS_LEAN_TAIL "ds_write_b64 %[orow], %[f] offset:%[at]\n\t" END             \
-                 : AS_LEAN_OUT OUTS                                                                           \
-                 : AS_LEAN_IN INS, [orow] "v"(orow), [at] "i"(8 * BIT)                                        \
-                 : "vcc", "memory");                                                                          \
-  else                                                                                                        \
-    asm(AS_LEAN_HEAD MOVS AS_LEAN_TAIL END : AS_LEAN_OUT OUTS : AS_LEAN_IN INS : "vcc")
-#define AS_COMMA ,
-  if constexpr (SMAX == 1) {
-    AS_LEAN_ASM("", , , AS_LEAN_END1);
-  } else if constexpr (SMAX == 2) {
-    AS_LEAN_ASM("v_mov_b64_e32 %[F1], %[f1]\n\t", AS_COMMA[F1] "+v"(st.F[1]), AS_COMMA[f1] "v"(fs[1]), AS_LEAN_END);
-  } else if constexpr (SMAX == 4) {
-    AS_LEAN_ASM("v_mov_b64_e32 %[F1], %[f1]\n\tv_mov_b64_e32 %[F2], %[f2]\n\tv_mov_b64_e32 %[F3], %[f3]\n\t",
-                AS_COMMA[F1] "+v"(st.F[1]) AS_COMMA[F2] "+v"(st.F[2]) AS_COMMA[F3] "+v"(st.F[3]),
-                AS_COMMA[f1] "v"(fs[1]) AS_COMMA[f2] "v"(fs[2]) AS_COMMA[f3] "v"(fs[3]), AS_LEAN_END);
-  } else {
-    AS_LEAN_ASM("v_mov_b64_e32 %[F1], %[f1]\n\tv_mov_b64_e32 %[F2], %[f2]\n\tv_mov_b64_e32 %[F3], %[f3]\n\t"
-                "v_mov_b64_e32 %[F4], %[f4]\n\tv_mov_b64_e32 %[F5], %[f5]\n\tv_mov_b64_e32 %[F6], %[f6]\n\t"
-                "v_mov_b64_e32 %[F7], %[f7]\n\t",
-                AS_COMMA[F1] "+v"(st.F[1]) AS_COMMA[F2] "+v"(st.F[2]) AS_COMMA[F3] "+v"(st.F[3])
-                    AS_COMMA[F4] "+v"(st.F[4]) AS_COMMA[F5] "+v"(st.F[5]) AS_COMMA[F6] "+v"(st.F[6])
-                        AS_COMMA[F7] "+v"(st.F[7]),
-                AS_COMMA[f1] "v"(fs[1]) AS_COMMA[f2] "v"(fs[2]) AS_COMMA[f3] "v"(fs[3]) AS_COMMA[f4] "v"(fs[4])
-                    AS_COMMA[f5] "v"(fs[5]) AS_COMMA[f6] "v"(fs[6]) AS_COMMA[f7] "v"(fs[7]),
-                AS_LEAN_END);
-  }
+  AS_LEAN_STAGES
 }
+#undef AS_LEAN_HEAD
+#undef AS_LEAN_TMP
+#undef AS_LEAN_SEL
+#undef AS_LEAN_CLOBBERS
+
+// One job in the wavefront: the minimum is uniform and the lowest of the equal
+// lanes a scalar bit search (none equal: no lane), which leaves the vector unit
+// to the other wavefronts of the SIMD.
+#define AS_LEAN_HEAD                             \
+  "s_nop 1\n\t"                                  \
+  "v_cmp_eq_f64_e32 vcc, %[mn], %[key]\n\t"      \
+  "s_ff1_i32_b64 %[i], vcc\n\t"                  \
+  "s_lshl_b64 %[m], 1, %[i]\n\t"                 \
+  "s_and_b64 exec, vcc, %[m]\n\t"
+#define AS_LEAN_TMP [i] "=&s"(i), [m] "=&s"(m)
+#define AS_LEAN_SEL [mn] "s"(mn)
+#define AS_LEAN_CLOBBERS "vcc", "scc"
+template <int SMAX, int BIT, bool STATS, bool ROW>
+__device__ __forceinline__ void lean_commit_one(LeanLane<SMAX>& st, double mn, double key, const double (&fs)[SMAX],
+                                                double dl, double slow, uint32_t& sr, uint32_t orow) {
+  uint32_t i;
+  uint64_t m;
+  const double f = fs[SMAX - 1];
+  AS_LEAN_STAGES
+}
+#undef AS_LEAN_HEAD
+#undef AS_LEAN_TMP
+#undef AS_LEAN_SEL
+#undef AS_LEAN_CLOBBERS
+#undef AS_LEAN_STAGES
 #undef AS_LEAN_ASM
 #undef AS_COMMA
-#undef AS_LEAN_HEAD
 #undef AS_LEAN_TAIL
+#undef AS_LEAN_SUMS
 #undef AS_LEAN_END
 #undef AS_LEAN_END1
 #undef AS_LEAN_OUT
@@ -191,23 +229,26 @@ __device__ __forceinline__ double lean_slow(const double (&L)[SMAX]) {
   return m;
 }
 
-// Minimum over each aligned group of W lanes, in every lane of it; NaN lanes
-// are passed over.
+// Minimum over each aligned group of W lanes, in every lane of it (W = 64: a
+// scalar); NaN lanes are passed over.
 template <int W>
 __device__ __forceinline__ double lean_min(double v) {
   if constexpr (W >= 2) v = vmin(v, dpp_f64<kXor1>(v));
   if constexpr (W >= 4) v = vmin(v, dpp_f64<kXor2>(v));
   if constexpr (W >= 8) v = vmin(v, dpp_f64<kHalfMirror>(v));
   if constexpr (W >= 16) v = vmin(v, dpp_f64<kMirror>(v));
-  if constexpr (W >= 32) {
+  if constexpr (W == 32) {
     const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
     const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
     v = vmin(__hiloint2double((int)h[0], (int)l[0]), __hiloint2double((int)h[1], (int)l[1]));
   }
-  if constexpr (W >= 64) {
-    const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
-    const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
-    v = vmin(__hiloint2double((int)h[0], (int)l[0]), __hiloint2double((int)h[1], (int)l[1]));
+  if constexpr (W == 64) {
+    // the rows' minima meet in the last row (what the broadcasts bring to rows
+    // without a source does not reach it)
+    v = vmin(v, dpp_f64<kBcast15>(v));
+    v = vmin(v, dpp_f64<kBcast31>(v));
+    v = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
+                         __builtin_amdgcn_readlane(__double2loint(v), 63));
   }
   return v;
 }
@@ -225,7 +266,10 @@ __device__ __forceinline__ void lean_step(LeanLane<SMAX>& st, const LeanReq<SMAX
   for (int s = 0; s < SMAX; ++s) f = fs[s] = vmax(f, st.F[s]) + q.L[s];
   const double slow = STATS ? lean_slow<SMAX>(q.L) : 0.0;
   const double dl = MS ? q.t + st.sigma * q.dl : q.dl;
-  lean_commit<SMAX, BIT, STATS, ROW>(st, mn, key, blo, bhi, fs, dl, slow, sr, orow);
+  if constexpr (W == 64)
+    lean_commit_one<SMAX, BIT, STATS, ROW>(st, mn, key, fs, dl, slow, sr, orow);
+  else
+    lean_commit<SMAX, BIT, STATS, ROW>(st, mn, key, blo, bhi, fs, dl, slow, sr, orow);
 }
 
 template <int W, int SMAX, bool STATS, bool ROW, bool MS, int K>

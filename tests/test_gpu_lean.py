@@ -68,6 +68,21 @@ def test_exact_ties(api, G, hosts, cfgs):
     _check(api, _problem(G, 700, G, 5, [4.0, 40.0], cfgs=cfgs, hosts=hosts, burst=True), f"ties G={G}")
 
 
+@pytest.mark.parametrize("stages", [1, 4])
+@pytest.mark.parametrize("G", [33, 64])
+def test_minimum_across_rows_of_lanes(api, G, stages):
+    """Wavefronts of one job (33 to 64 groups): model m on group m alone, on one
+    group of each 16, or on the first and the last group, with ties between them."""
+    pb = _problem(G + stages, 900, G, 3, [1.5, 6.0], M=G, cfgs=((stages, 1),), burst=True)
+    gcfg = np.zeros_like(pb.group_cfg)
+    mask = np.zeros_like(pb.host_mask)
+    for m in range(G):
+        mask[0, m] = np.uint64(1 << m)
+        mask[1, m] = np.uint64(sum(1 << g for g in range(m % 16, G, 16)))
+        mask[2, m] = np.uint64(1 | 1 << (G - 1))
+    _check(api, dataclasses.replace(pb, group_cfg=gcfg, host_mask=mask), f"rows of lanes G={G} stages={stages}")
+
+
 @pytest.mark.parametrize("G,P", [(1, 4100), (4, 1500), (16, 2051), (32, 1537), (64, 1100)])
 def test_several_jobs_per_wavefront(api, G, P):
     """More jobs than SIMDs: several per wavefront, the last wavefront part empty."""
