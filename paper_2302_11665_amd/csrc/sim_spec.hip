@@ -880,12 +880,25 @@ constexpr int64_t kSpecMinSegment = 2048;
 // above); doubled up to kSpecCheckpointMax until they fit kSpecCheckpointBytes.
 constexpr int64_t kSpecCheckpoint = 2048, kSpecCheckpointMax = 8192;
 constexpr int64_t kSpecCheckpointBytes = 512ll << 20;
-// Fix-ups may simulate J * n / kSpecBudget requests in all, and start from at
-// most kSpecPairs of all segments, before the call is left to the
-// group-per-lane kernels: where groups stay saturated runs from different
-// states never meet, and simulating everything again there is cheaper.
-constexpr int64_t kSpecBudget = 16;
-constexpr double kSpecPairs = 0.3;
+// When the fix-ups give up and leave the call to the group-per-lane kernels,
+// because under traffic that keeps groups saturated runs from different states
+// never meet.  What they have cost by then is lost, and those kernels' time is
+// what giving up costs, so the line lies at shares of that time (a re-run's
+// request takes kSpecFixNs of a SIMD):
+//   * kSpecTotal of it in all, and kSpecFirst in the first round.  Calls that
+//     were worth finishing took 0.05 to 0.15 in the first round and up to 0.3 in
+//     all, the others 0.22 to 8 in the first round;
+//   * at once where more than kSpecPairs of all segments start wrong (worth
+//     finishing: up to 0.45), or more than kSpecAgain of them again after the
+//     first round, so that the rounds leave most of the trace to the job-by-job
+//     step (300 jobs, 200,000 requests: 0.71 and 0.73 took 13 and 15 ms, 0.80
+//     took 31, where the group-per-lane kernels take 18).
+// Measured, giving up and finished: 1000 placements of 16 four-stage groups,
+// 900,000 requests, seven seeds and loads 91 to 108 and 22 to 78 ms; 4000 of
+// them 106 and 37; 300,000 requests 36 and 17; and where groups stay saturated
+// 88 and 108 to 545.
+constexpr double kSpecTotal = 1.0 / 3.0, kSpecFirst = 0.18, kSpecFixNs = 90.0;
+constexpr double kSpecPairs = 0.5, kSpecAgain = 0.75;
 
 }  // namespace
 
@@ -939,12 +952,20 @@ int spec_segments(int64_t n, int64_t J, int jpw, int per_cu, int64_t min_seg, in
   return (int)std::max<int64_t>(1, std::min<int64_t>(k, max_seg));
 }
 
+// Nanoseconds that the group-per-lane kernels take for a call: a request of one
+// wavefront takes 50 + 5.5 per doubling of its lanes + 4.5 per stage alone on
+// its SIMD (79 at 4 lanes and 4 stages, 90 at 16 and 4) and three quarters of
+// that per wavefront beyond.
+double lean_ns(const KArgs& k, int smax) {
+  const int W = pow2ceil(k.G);
+  const double waves = std::ceil((double)k.J / (64 / W));
+  return (double)k.n * (50.0 + 5.5 * std::log2((double)W) + 4.5 * smax) *
+         std::max(1.0, 0.75 * waves / (4.0 * compute_units()));
+}
+
 // Whether the speculative kernels beat the group-per-lane kernels on this
-// call, by a model in nanoseconds of one wavefront: a request of a
-// group-per-lane wavefront takes 50 + 5.5 per doubling of its lanes + 4.5 per
-// stage alone on its SIMD (79 at 4 lanes and 4 stages, 90 at 16 and 4) and
-// three quarters of that per wavefront beyond; one of pass 0, with 64 jobs,
-// 150 + 35 per stage (287 at 4 stages), over a segment and its warm-up; the
+// call, by a model in nanoseconds of one wavefront: a request of pass 0, with 64
+// jobs, 150 + 35 per stage (287 at 4 stages), over a segment and its warm-up; the
 // fix-ups are taken as 2 ms.  The speculative kernels must promise 0.4 of the
 // other time, because traffic under which runs do not meet costs both: 777
 // late selections of 32 two-stage groups, 76,801 requests, promise 0.64 and do
@@ -954,16 +975,11 @@ int spec_segments(int64_t n, int64_t J, int jpw, int per_cu, int64_t min_seg, in
 // never pays.
 bool spec_pays(const KArgs& k, int smax, int nseg, int jpw, int per_cu) {
   if (nseg < 2) return false;
-  const double simds = 4.0 * compute_units();
-  const int Wp = pow2ceil(k.G);
-  const double waves_lean = std::ceil((double)k.J / (64 / Wp));
-  const double lean = 50.0 + 5.5 * std::log2((double)Wp) + 4.5 * smax;
-  const double t_lean = (double)k.n * lean * std::max(1.0, 0.75 * waves_lean / simds);
   const double slots = (double)compute_units() * std::max(per_cu, 1);
   const double waves_spec = std::ceil((double)k.J / jpw) * nseg;
   const double seg = (double)k.n / nseg + (double)std::min<int64_t>(kSpecWarmup, k.n);
   const double t_spec = seg * (150.0 + 35.0 * smax) * std::ceil(waves_spec / slots) + 2e6;
-  return t_spec < 0.4 * t_lean;
+  return t_spec < 0.4 * lean_ns(k, smax);
 }
 
 size_t ws_up(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -1116,12 +1132,20 @@ int run_spec(KArgs& k, int smax, hipStream_t stream, bool can_give_up, void* cal
   a.ck = pl.ck;
   a.ckps = (int32_t)pl.ckps;
   a.cap = INT64_MAX;
-  a.budget = can_give_up ? (int64_t)k.J * (k.n / kSpecBudget) : INT64_MAX;
-  a.pairs = can_give_up ? (int64_t)(kSpecPairs * (double)k.J * (a.nseg - 1)) : INT64_MAX;
+  a.budget = a.budget1 = a.pairs = INT64_MAX;
+  a.again = 2.0;  // never
+  if (can_give_up) {
+    const double all = lean_ns(k, smax) * 4 * compute_units() / kSpecFixNs;
+    a.budget = (int64_t)(kSpecTotal * all);
+    a.budget1 = (int64_t)(kSpecFirst * all);
+    a.pairs = (int64_t)(kSpecPairs * (double)k.J * (a.nseg - 1));
+    a.again = kSpecAgain;
+  }
   // ALPASERVE_SPEC_CAP (requests of one re-run) alone decides where it is set (tests)
   if (const char* c = getenv("ALPASERVE_SPEC_CAP"); c && can_give_up) {
     a.cap = std::max<int64_t>(64, atoll(c));
-    a.budget = a.pairs = INT64_MAX;
+    a.budget = a.budget1 = a.pairs = INT64_MAX;
+    a.again = 2.0;
   }
   if ((int64_t)a.njb * a.nseg > 0x7FFFFFFFLL) return AS_E_LIMITS;
   a.nw = (k.n + 63) / 64;

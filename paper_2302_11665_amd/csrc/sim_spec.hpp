@@ -50,7 +50,9 @@ struct SpecArgs {
   int32_t ckps;         // checkpoints per segment (upper bound)
   int64_t cap;          // requests one re-run may simulate before the fix-ups give up
   int64_t budget;       // and all of them together
+  int64_t budget1;      // and those of round 1, by what its entries promise so far
   int64_t pairs;        // entries of the first list beyond which they give up at once
+  double again;         // and share of it listed again beyond which they do
   int64_t nw;
   int64_t warmup;  // requests simulated before a segment to estimate its start state
   int32_t M, C, smax_in, G, K, J, n_finish, nseg, njb;
@@ -92,10 +94,12 @@ __device__ __forceinline__ int spec_ckpts(int64_t b, int64_t e, int64_t ck) { re
 // them sent the whole call to the other kernels, -> 164 to 182.
 //
 // The re-run of one segment.  Returns 0: gave up; 1: met the old results; 2: ran
-// to the end, which st.F holds.
+// to the end, which st.F holds.  first: entries of the first list in round 1,
+// else 0 (that round's entries promise what those taken so far have run, the
+// ones that still run in part, so the promise is never too high).
 template <int W, int SMAX, bool UNI>
 __device__ __forceinline__ int fix_segment(const SpecArgs& a, const LeanWave<W, SMAX>& w, LeanLane<SMAX>& st,
-                                           int job, int k, const double (&start)[SMAX]) {
+                                           int job, int k, const double (&start)[SMAX], int first) {
   const int lane = threadIdx.x & 63;
   const bool mine_g = lane < a.G;  // this lane holds a group
   const int GS = a.G * SMAX;
@@ -148,7 +152,12 @@ __device__ __forceinline__ int fix_segment(const SpecArgs& a, const LeanWave<W, 
         a.ck_fsum[cj] = fsum;
         all = atomicAdd(a.work, (unsigned long long)a.ck);
       }
-      if (lean_uniform(all) > (unsigned long long)a.budget) return 0;
+      all = lean_uniform(all);
+      if (all > (unsigned long long)a.budget) return 0;
+      if (first > 0) {
+        const int taken = __hip_atomic_load(a.taken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((double)all * first > (double)a.budget1 * (taken < first ? taken : first)) return 0;
+      }
     }
     if (cb - b >= a.cap) return 0;
     const double tv = tn;
@@ -196,7 +205,7 @@ __device__ __forceinline__ bool round_entry(const SpecArgs& a, const LeanWave<W,
   if (!fix_stale<SMAX>(a, a.xch[(q - 1) & 1], job, k, start)) return true;
   LeanLane<SMAX> st;
   st.busy = 0.0;
-  const int r = fix_segment<W, SMAX, UNI>(a, w, st, job, k, start);
+  const int r = fix_segment<W, SMAX, UNI>(a, w, st, job, k, start, q == 1 ? a.count[0] : 0);
   if (r != 2) return r != 0;
   // a new end state, unless it is the old one: the next segment is listed
   const int GS = a.G * SMAX;
@@ -226,7 +235,7 @@ __device__ __forceinline__ bool fix_job(const SpecArgs& a, const LeanWave<W, SMA
   for (int k = 1; k < a.nseg; ++k) {
     double start[SMAX];
     if (!fix_stale<SMAX>(a, a.st_end, job, k, start)) continue;
-    const int r = fix_segment<W, SMAX, UNI>(a, w, st, job, k, start);
+    const int r = fix_segment<W, SMAX, UNI>(a, w, st, job, k, start, 0);
     if (r == 0) return false;
     if (r == 2 && lane < a.G) {
       const size_t own = ((size_t)k * a.G * SMAX + (size_t)lane * SMAX) * a.J + job;
@@ -244,7 +253,7 @@ __global__ __launch_bounds__(64) void spec_fix(const SpecArgs a, int q) {
   const int n = __builtin_amdgcn_readfirstlane(a.count[q - 1]);
   if (n == 0 || __builtin_amdgcn_readfirstlane(a.cfg_info[2]) != 0) return;
   const int lane = threadIdx.x & 63;
-  if (q == 1 && n > a.pairs) {
+  if ((q == 1 && n > a.pairs) || (q == 2 && n > a.again * a.count[0])) {
     if (blockIdx.x == 0 && lane == 0) a.cfg_info[2] = 1;
     return;
   }

@@ -1,9 +1,11 @@
 """GPU test of the speculative kernels' fallback: when their workspace cannot
 be had (forced here with ALPASERVE_SPEC_MAX_WORKSPACE, which makes a larger
 workspace fail as a failed allocation does), as_simulate_placements must
-still succeed, on the shared-trace kernels, with the same results bit for
+still succeed, on the group-per-lane kernels, with the same results bit for
 bit (served counts, attainment, digests, output rows) as the speculative
-kernels give, and those must equal the oracle's on sampled jobs."""
+kernels give, and those must equal the oracle's on sampled jobs.  The same
+where the fix-ups give up by their own limits, none of them forced, and where
+they must not."""
 import os
 import sys
 
@@ -11,7 +13,7 @@ import numpy as np
 import pytest
 
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
-from gpu_common import say  # noqa: E402
+from gpu_common import kernels_run, say  # noqa: E402
 
 import oracle  # noqa: E402
 
@@ -67,3 +69,52 @@ def test_workspace_failure_falls_back(sim, monkeypatch):
         assert int(served[j]) == s and tuple(int(x) for x in digest[j]) == dg, j
         if j in rows:
             assert fin[rows[j]].tobytes() == f.tobytes(), j
+
+
+def _traffic(kind, seconds, P, stretch):
+    """The heavy trace's models and groups under other placements, its arrivals
+    `stretch` times as far apart."""
+    from paper_2302_11665_amd.workload import problems
+    pb = problems.c4_heavy(duration=seconds, n_placements=P, n_finish=4)
+    pb.t = pb.t * stretch
+    r = np.random.default_rng(5)
+    M, G = len(pb.d_single), pb.group_cfg.shape[1]
+    if kind == "additions":  # one selection, and in each placement one replica more
+        order = r.permutation(M * G)
+        mask = np.zeros((P, M), np.uint64)
+        for x in order[:200]:
+            mask[:, x // G] |= np.uint64(1 << int(x % G))
+        for p in range(P):
+            x = int(order[200 + p % (M * G - 200)])
+            mask[p, x // G] |= np.uint64(1 << (x % G))
+        pb.host_mask = mask
+    else:  # two replicas of each model
+        g = np.argsort(r.random((P, M, G)), axis=2)[:, :, :2].astype(np.uint64)
+        pb.host_mask = np.bitwise_or.reduce(np.left_shift(np.uint64(1), g), axis=2)
+    return pb
+
+
+@pytest.mark.parametrize("kind,seconds,P,stretch,gives_up", [
+    ("additions", 214.0, 1000, 1.2, False), ("additions", 143.0, 300, 1.1, False),
+    ("two replicas", 214.0, 1000, 1.0, True),  # by the length of the first list
+    ("additions", 214.0, 1000, 1.02, True),    # by the first round's requests
+    ("two replicas", 143.0, 300, 1.1, True),   # by what the first round lists again
+    ("two replicas", 214.0, 1000, 1.1, True),  # by all rounds' requests
+])
+def test_when_the_fix_ups_give_up(sim, monkeypatch, kind, seconds, P, stretch, gives_up):
+    for v in ("PATH", "SPEC_SEGMENTS", "SPEC_WARMUP", "SPEC_CAP", "SPEC_CKPT", "SPEC_MAX_WORKSPACE"):
+        monkeypatch.delenv("ALPASERVE_" + v, raising=False)
+    pb = _traffic(kind, seconds, P, stretch)
+    say(f"fix-ups, {kind} x{stretch}: {pb.n_jobs} jobs x {len(pb.t)} requests")
+    times = kernels_run(lambda: _run(sim, pb))
+    assert any("spec_pass0" in n for n in times), sorted(times)
+    gated = sum(t for n, t in times.items() if "shared_kernel" in n)  # returns at once unless they gave up
+    assert (gated > 1000.0) == gives_up, times
+    got = _run(sim, pb)
+    monkeypatch.setenv("ALPASERVE_PATH", "shared")
+    for a, b in zip(got, _run(sim, pb)):
+        assert np.asarray(a).tobytes() == np.asarray(b).tobytes()
+    for j in (0, P - 1):
+        s, dg, _ = oracle.lib().simulate_job(pb.t, pb.model, pb.d_single, pb.cfg_stages, pb.stage_lat,
+                                             pb.group_cfg[j], pb.host_mask[j], pb.slo_scale[0])
+        assert int(got[0][j]) == s and tuple(int(x) for x in got[2][j]) == dg, j
