@@ -444,8 +444,10 @@ int run_trace_kernels(KArgs& a, int W, int smax, hipStream_t stream, bool only_c
   const int64_t J = a.J;
   const int Ws = pow2ceil(a.G), jw = lean_jobs_per_wave(Ws, J);
   const bool mixes = lean_mixes_scales(Ws, J, a.K, jw);
-  // the jobs, and those with a per-request row once more
+  // the jobs, and those with a per-request row once more (most return at once
+  // unless the rows are apart)
   const int64_t nw = (mixes ? (J + jw - 1) / jw : lean_wave_count(J, a.K, jw)) + (a.n > 0 ? a.n_finish : 0);
+  a.rows_apart = nw <= simd_count();
   const int waves = lean_waves_per_block(nw, Ws, a, smax, false);
   const size_t lds_shared = as_dev::lean_lds_bytes(Ws, a.M, pow2ceil(a.C), smax, false, waves);
   if (use_shared_path() && lean_takes(a, smax) && lds_shared <= shared_lds_limit()) {
@@ -708,7 +710,6 @@ int as_simulate_jobs(const double* t, const int32_t* model, const int64_t* seg_o
   if (use_shared_path() && (general || (Ws == 64 && lean_takes(a, smax, 1024))) && lds_seg <= shared_lds_limit() &&
       seg_one_per_wave(Ws, n_jobs)) {
     hipError_t e = hipSuccess;
-    const int64_t n_rows = finish_stride > 0 ? a.n_finish : 0;
     // Jobs longest first.  With more jobs than seg_waves_per_simd()
     // wavefronts per SIMD, that many wavefronts take them in turn (each
     // compute unit holds that many workgroups of one wavefront per SIMD: the
@@ -718,12 +719,15 @@ int as_simulate_jobs(const double* t, const int32_t* model, const int64_t* seg_o
     // its array cannot be allocated.
     const int wps = as_dev::seg_waves_per_simd();
     const int64_t queue_blocks = as_dev::seg_queue_blocks(wps);
-    int waves = lean_waves_per_block(n_jobs + n_rows, Ws, a, smax, false);
-    int64_t blocks = (n_jobs + n_rows + waves - 1) / waves;
+    const int64_t n_rows = finish_stride > 0 ? a.n_finish : 0;
+    a.rows_apart = n_rows > 0 && n_jobs + n_rows <= simd_count();
+    const int64_t nw = n_jobs + (a.rows_apart ? n_rows : 0);
+    int waves = lean_waves_per_block(nw, Ws, a, smax, false);
+    int64_t blocks = (nw + waves - 1) / waves;
     size_t lds = lds_seg;
     int32_t* order = nullptr;
     const bool queue = blocks > queue_blocks;
-    if (n_jobs <= as_dev::kOrderMaxJobs && (queue || n_jobs + n_rows > simd_count()) &&
+    if (n_jobs <= as_dev::kOrderMaxJobs && (queue || n_jobs > simd_count()) &&
         pool_alloc(reinterpret_cast<void**>(&order), ((size_t)n_jobs + 1) * 4, s) != hipSuccess) {
       (void)hipGetLastError();
       order = nullptr;

@@ -77,6 +77,7 @@ struct KArgs {
   double* out_group_busy;     // statistics launches: [J][G]
   int32_t M, C, smax_in, G, K, J, n_finish;
   int32_t P, n_segments;
+  int32_t rows_apart;   // group-per-lane kernels: per-request rows are written by wavefronts of their own
   int64_t min_segment;  // the speculative kernels cut no shorter segments (0: their own least)
   int32_t cfg_stages[AS_MAX_CONFIGS];
   int32_t finish_jobs[AS_MAX_FINISH];

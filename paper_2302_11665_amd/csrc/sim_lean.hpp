@@ -272,25 +272,37 @@ __device__ __forceinline__ void lean_step(LeanLane<SMAX>& st, const LeanReq<SMAX
     lean_commit<SMAX, BIT, STATS, ROW>(st, mn, key, blo, bhi, fs, dl, slow, sr, orow);
 }
 
-template <int W, int SMAX, bool STATS, bool ROW, bool MS, int K>
-__device__ __forceinline__ void lean_steps(LeanLane<SMAX>& st, const LeanReq<SMAX> (&q)[kLeanB], uint32_t blo,
+template <int W, int SMAX, bool STATS, bool ROW, bool MS, int K, int N, int AT = 0>
+__device__ __forceinline__ void lean_steps(LeanLane<SMAX>& st, const LeanReq<SMAX> (&q)[N], uint32_t blo,
                                            uint32_t bhi, uint32_t& sr, uint32_t orow) {
-  if constexpr (K < kLeanB) {
-    lean_step<W, SMAX, K, STATS, ROW, MS>(st, q[K], blo, bhi, sr, orow);
-    lean_steps<W, SMAX, STATS, ROW, MS, K + 1>(st, q, blo, bhi, sr, orow);
+  if constexpr (AT < N) {
+    lean_step<W, SMAX, K + AT, STATS, ROW, MS>(st, q[AT], blo, bhi, sr, orow);
+    lean_steps<W, SMAX, STATS, ROW, MS, K, N, AT + 1>(st, q, blo, bhi, sr, orow);
   }
 }
 
 // kLeanB staged requests.  Returns their accept bits (bit k: request k was
-// accepted by this lane).
-template <int W, int SMAX, bool UNI, bool STATS, bool ROW, bool MS>
+// accepted by this lane).  A wavefront that writes a row beside its results reads
+// them by halves at 2 and 4 stages: all at once, its registers (134 and 170, not
+// 124 and 160) would take a wavefront from every SIMD, also without rows (16,384
+// jobs of 16 four-stage groups: 5.4 ms instead of 5.2).
+template <int W, int SMAX, bool UNI, bool STATS, int ROW, bool MS>
 __device__ __forceinline__ uint32_t lean_batch(LeanLane<SMAX>& st, const unsigned char* r, const char* lrow,
                                                uint32_t blo, uint32_t bhi, uint32_t orow) {
+  constexpr int N = ROW == 1 && (SMAX == 2 || SMAX == 4) ? kLeanB / 2 : kLeanB;
   uint32_t sr = 0;
-  LeanReq<SMAX> q[kLeanB];
+  {
+    LeanReq<SMAX> q[N];
 #pragma unroll
-  for (int k = 0; k < kLeanB; ++k) q[k] = lean_read<SMAX, UNI>(r + k * lean_stride(SMAX), lrow);
-  lean_steps<W, SMAX, STATS, ROW, MS, 0>(st, q, blo, bhi, sr, orow);
+    for (int k = 0; k < N; ++k) q[k] = lean_read<SMAX, UNI>(r + k * lean_stride(SMAX), lrow);
+    lean_steps<W, SMAX, STATS, ROW != 0, MS, 0>(st, q, blo, bhi, sr, orow);
+  }
+  if constexpr (N < kLeanB) {
+    LeanReq<SMAX> q[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) q[k] = lean_read<SMAX, UNI>(r + (N + k) * lean_stride(SMAX), lrow);
+    lean_steps<W, SMAX, STATS, ROW != 0, MS, N>(st, q, blo, bhi, sr, orow);
+  }
   return sr;
 }
 
@@ -311,8 +323,9 @@ struct LeanIn {
   double sigma;
   int cfg;      // this lane's group's configuration, -1: no group
   uint64_t hm;  // lane m: lanes whose group hosts model m
-  double* row;  // per-request output (ROW: jw is 1)
+  double* row;  // ROW: per-request output of the job in slot row_slot (0 for 2)
   int64_t row_n;
+  int row_slot;
   bool digest;  // the ordered hash is wanted
 };
 
@@ -330,6 +343,7 @@ struct LeanWave {
   const char* urow;  // the first group's (UNI: every group's)
   int lshift;        // a model's rows are 1 << lshift bytes apart
   unsigned char* rec;  // lean_wave_bytes of LDS, then finish times by rank (ROW)
+  uint64_t row_lanes;  // ROW: the lanes of the job whose row is written
   double slo;          // lane m: model m's SLO (MS: its d_single)
   uint64_t hm;         // lane m: lanes whose group hosts model m
   uint64_t hosted;     // models some job hosts
@@ -368,10 +382,12 @@ __device__ __forceinline__ bool lean_uni(int cfg) {
 
 // One chunk: lane e holds request e (mine: it exists and some job hosts it;
 // rank: hosted requests before it).  Returns the job's accept bits in all its
-// lanes, the request of rank k at bit k.  ROW: finish times (-1: rejected) by
-// rank are left behind the staged requests.  Called by whole wavefronts in
+// lanes, the request of rank k at bit k.  ROW: the row's job's finish times (-1:
+// rejected, -2: it does not host the model) by rank are left behind the staged
+// requests, and the other jobs' lanes store theirs past them; 2: the row alone of
+// a wavefront's only job, 1: beside all results.  Called by whole wavefronts in
 // uniform control flow (the commit restores a full exec mask).
-template <int W, int SMAX, bool UNI, bool STATS, bool ROW, bool MS = false>
+template <int W, int SMAX, bool UNI, bool STATS, int ROW, bool MS = false>
 __device__ __forceinline__ uint64_t lean_chunk(LeanLane<SMAX>& st, const LeanWave<W, SMAX>& w, double tv, int mv,
                                                bool mine, int rank, int nh) {
   constexpr int R = lean_stride(SMAX);
@@ -379,7 +395,8 @@ __device__ __forceinline__ uint64_t lean_chunk(LeanLane<SMAX>& st, const LeanWav
   const int lane = threadIdx.x & 63;
   uint64_t word = 0;  // this lane's accept bits
   double* orow = reinterpret_cast<double*>(w.rec + (64 + kLeanB) * R);
-  const uint32_t olds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) double*)orow;
+  uint32_t olds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) double*)orow;
+  if constexpr (ROW == 1) olds += __builtin_amdgcn_inverse_ballot_w64(w.row_lanes) ? 0 : (64 + kLeanB) * 8;
   // stage the hosted requests, then requests that no lane hosts up to a
   // whole batch
   const int from = (mv & 63) << 2;
@@ -403,16 +420,14 @@ __device__ __forceinline__ uint64_t lean_chunk(LeanLane<SMAX>& st, const LeanWav
     } else {
       *(uint4*)(r + 16) = make_uint4(hl, hh, off, 0u);
     }
+    if constexpr (ROW == 1) orow[rank] = (((uint64_t)hh << 32 | hl) & w.row_lanes) != 0 ? -1.0 : -2.0;
   }
   if (lane < kLeanB) {
     unsigned char* r = w.rec + (nh + lane) * R;
     *(double2*)r = make_double2(0.0, 0.0);
     *(uint4*)(r + 16) = make_uint4(0u, 0u, 0u, 0u);
   }
-  if constexpr (ROW) {
-    orow[lane] = -1.0;
-    if (lane < kLeanB) orow[64 + lane] = -1.0;
-  }
+  if constexpr (ROW == 2) orow[lane] = -1.0;
   lean_fence();
   const int nb = (nh + kLeanB - 1) / kLeanB;
   for (int b = 0; b < nb; ++b) {
@@ -435,11 +450,12 @@ __device__ __forceinline__ bool lean_mine(const LeanWave<W, SMAX>& w, bool in, i
 }
 
 // cnt: STATS, this wavefront's [jw][M] served counters in LDS, zeroed.
-template <int W, int SMAX, bool UNI, bool STATS, bool ROW, bool MS>
+template <int W, int SMAX, bool UNI, bool STATS, int ROW, bool MS>
 __device__ __forceinline__ LeanOut lean_run(const KArgs& a, const LeanIn& in, const double* sL, int lshift,
                                             unsigned char* rec, uint32_t* cnt) {
   const int lane = threadIdx.x & 63;
-  const LeanWave<W, SMAX> w = lean_wave<W, SMAX, MS>(a, in.sigma, in.cfg, in.hm, sL, lshift, rec);
+  LeanWave<W, SMAX> w = lean_wave<W, SMAX, MS>(a, in.sigma, in.cfg, in.hm, sL, lshift, rec);
+  if constexpr (ROW == 1) w.row_lanes = (W == 64 ? ~0ull : ((1ull << (W & 63)) - 1)) << (in.row_slot * (W & 63));
   LeanLane<SMAX> st;
 #pragma unroll
   for (int s = 0; s < SMAX; ++s) st.F[s] = 0.0;
@@ -480,19 +496,20 @@ __device__ __forceinline__ LeanOut lean_run(const KArgs& a, const LeanIn& in, co
       word = full;
     }
     if (in.digest) hash = (hash ^ word) * kHashMul;
-    if constexpr (ROW) {
+    if constexpr (ROW != 0) {
       lean_fence();
       const double* orow = reinterpret_cast<const double*>(rec + (64 + kLeanB) * lean_stride(SMAX));
-      if (base + lane < in.row_n) in.row[base + lane] = mine ? orow[rank] : -2.0;
+      if (lane < (int)(in.row_n - base < 64 ? in.row_n - base : 64)) (in.row + base)[lane] = mine ? orow[rank] : -2.0;
     }
   }
   return LeanOut{served, hash, seg_sum_u64<W>(st.fin), st.busy};
 }
 
 // LDS bytes of a workgroup of `waves` wavefronts: the stage-latency table,
-// each wavefront's staged requests and rows, and for statistics its counters.
+// each wavefront's staged requests, and for statistics its counters, else its
+// row (twice: once for what the other jobs' lanes store).
 __host__ __device__ constexpr size_t lean_wave_lds(int W, int M, int SMAX, bool stats) {
-  return lean_wave_bytes(SMAX) + (64 + kLeanB) * 8 + (stats ? ((size_t)(64 / W) * M * 4 + 15) / 16 * 16 : 0);
+  return lean_wave_bytes(SMAX) + (stats ? ((size_t)(64 / W) * M * 4 + 15) / 16 * 16 : (size_t)2 * (64 + kLeanB) * 8);
 }
 __host__ __device__ constexpr size_t lean_lds_bytes(int W, int M, int Cp, int SMAX, bool stats, int waves) {
   return ((size_t)M * Cp * SMAX * 8 + 15) / 16 * 16 + (size_t)waves * lean_wave_lds(W, M, SMAX, stats);
@@ -515,7 +532,7 @@ __device__ __forceinline__ int lean_table(const Args& a, double* sL, size_t& byt
   return lshift;
 }
 
-template <int W, int SMAX, bool STATS, bool ROW, bool MS = false>
+template <int W, int SMAX, bool STATS, int ROW, bool MS = false>
 __device__ __forceinline__ LeanOut lean_go(const KArgs& a, const LeanIn& in, const double* sL, int lshift,
                                            unsigned char* rec, uint32_t* cnt) {
   if (lean_uni(in.cfg))
@@ -523,11 +540,27 @@ __device__ __forceinline__ LeanOut lean_go(const KArgs& a, const LeanIn& in, con
   return lean_run<W, SMAX, false, STATS, ROW, MS>(a, in, sL, lshift, rec, cnt);
 }
 
+// The first of the launch's row jobs (f < n) for which own(job) holds, -1: none.
+// Called by whole wavefronts.
+template <class Own>
+__device__ __forceinline__ int lean_row(const KArgs& a, int n, Own own) {
+  const int lane = threadIdx.x & 63;
+  for (int b = 0; b < n; b += 64) {
+    const uint64_t hit = __builtin_amdgcn_ballot_w64(b + lane < n && own(a.finish_jobs[b + lane < n ? b + lane : 0]));
+    if (hit) return b + __builtin_ctzll(hit);
+  }
+  return -1;
+}
+
 // Workgroup blk of the jobs v of one shared trace.  Wavefront w runs jw
-// placements at one scale or, with MS, jw jobs in a row whatever their scale;
-// after the last of them, wavefront by wavefront, the jobs with a per-request
-// row once more for the row alone (so that no other job waits for the row's
-// code).
+// placements at one scale or, with MS, jw jobs in a row whatever their scale,
+// and writes the per-request row of the first of them that has one; after the
+// last of them, wavefront by wavefront, the other jobs with a row once more for
+// the row alone (rows_apart, where SIMDs are left for them: all jobs with a row).
+// A row makes its wavefront 4 to 9 % longer, and a wavefront more on a SIMD that
+// has others makes the launch a third to a half longer: 2048 jobs of 64 one-stage
+// groups, 20,000 requests, take 2.81 ms, with 4 rows 2.92 this way and 4.01 with
+// wavefronts of their own; 512 jobs 2.23, 2.31 and 2.24.
 template <int W, int SMAX, bool STATS, bool ROWS, bool MS = false>
 __device__ __forceinline__ void lean_body(const KArgs& a, const JobSet& v, int64_t blk) {
   static_assert(!(STATS && MS), "statistics launches run one scale a wavefront");
@@ -538,12 +571,12 @@ __device__ __forceinline__ void lean_body(const KArgs& a, const JobSet& v, int64
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   unsigned char* rec = smem + tab + (size_t)wave * lean_wave_lds(W, a.M, SMAX, STATS);
-  uint32_t* cnt = reinterpret_cast<uint32_t*>(rec + lean_wave_bytes(SMAX) + (64 + kLeanB) * 8);
+  uint32_t* cnt = reinterpret_cast<uint32_t*>(rec + lean_wave_bytes(SMAX));
   const int64_t w = blk * (int64_t)(blockDim.x >> 6) + wave;
   const int64_t P = v.J / a.K, per = (P + v.jw - 1) / v.jw;
   const int64_t nw = MS ? (v.J + v.jw - 1) / v.jw : per * a.K;
-  const bool rows = ROWS && w >= nw;
-  if (rows ? w - nw >= a.n_finish : w >= nw) return;
+  const bool again = ROWS && w >= nw;
+  if (again ? w - nw >= a.n_finish : w >= nw) return;
 
   LeanIn in;
   in.t = a.t;
@@ -551,22 +584,35 @@ __device__ __forceinline__ void lean_body(const KArgs& a, const JobSet& v, int64
   in.n = a.n;
   in.row = nullptr;
   in.row_n = a.n;
-  // the jobs of the wavefront: slot s has job job0 + s * step
-  int64_t job0, step = a.K;
-  if (rows) {
-    job0 = a.finish_jobs[w - nw];
+  in.row_slot = 0;
+  // the jobs of the wavefront: slot s has job job0 + s * step; of_wave: whether
+  // a job is one of wavefront x's
+  const uint32_t K = (uint32_t)a.K, jw = (uint32_t)v.jw;
+  auto wave_of = [&](uint32_t j) -> int64_t { return MS ? j / jw : (int64_t)(j % K) * per + j / K / jw; };
+  int64_t job0, step = MS ? 1 : a.K;
+  if (again) {
+    const int f = (int)(w - nw);
+    job0 = a.finish_jobs[f];
+    const int64_t x = wave_of((uint32_t)job0);
+    if (!a.rows_apart && lean_row(a, f, [&](int j) { return wave_of((uint32_t)j) == x; }) < 0) return;  // x writes it
     in.jw = 1;
-    in.row = a.out_finish + (w - nw) * a.n;
-  } else if (MS) {
-    job0 = w * v.jw;
-    step = 1;
-    in.jw = (int)(v.J - job0 < v.jw ? v.J - job0 : v.jw);
+    in.row = a.out_finish + f * a.n;
   } else {
     const int64_t k = w / per, p0 = (w % per) * v.jw;
-    job0 = p0 * a.K + k;
-    in.jw = (int)(P - p0 < v.jw ? P - p0 : v.jw);
+    job0 = MS ? w * v.jw : p0 * a.K + k;
+    const int64_t left = MS ? v.J - job0 : P - p0;
+    in.jw = (int)(left < v.jw ? left : v.jw);
+    if constexpr (ROWS) {
+      const int f = a.n > 0 && !a.rows_apart
+                        ? lean_row(a, a.n_finish, [&](int j) { return wave_of((uint32_t)j) == w; })
+                        : -1;
+      if (f >= 0) {
+        in.row = a.out_finish + f * a.n;
+        in.row_slot = (int)((a.finish_jobs[f] - job0) / step);
+      }
+    }
   }
-  in.digest = !rows && v.out_digest != nullptr;
+  in.digest = !again && v.out_digest != nullptr;
   const int slot = lane / W, g = lane % W;
   const bool mine = slot < in.jw && g < v.G;
   const int64_t job = job0 + slot * step;
@@ -593,11 +639,19 @@ __device__ __forceinline__ void lean_body(const KArgs& a, const JobSet& v, int64
     for (int i = lane; i < in.jw * a.M; i += 64) cnt[i] = 0;
     lean_fence();
   }
-  if (rows) {
-    if constexpr (ROWS) (void)lean_go<W, SMAX, false, true>(a, in, sL, lshift, rec, cnt);
-    return;
+  LeanOut o;
+  bool done = false;
+  if constexpr (ROWS) {
+    if (again) {
+      (void)lean_go<W, SMAX, false, 2>(a, in, sL, lshift, rec, cnt);
+      return;
+    }
+    if (in.row) {
+      o = lean_go<W, SMAX, false, 1, MS>(a, in, sL, lshift, rec, cnt);
+      done = true;
+    }
   }
-  const LeanOut o = lean_go<W, SMAX, STATS, false, MS>(a, in, sL, lshift, rec, cnt);
+  if (!done) o = lean_go<W, SMAX, STATS, 0, MS>(a, in, sL, lshift, rec, cnt);
   if (slot < in.jw && g == 0) {
     v.out_served[job] = o.served;
     if (v.out_attain) v.out_attain[job] = a.n > 0 ? (double)o.served / (double)a.n : 0.0;
@@ -624,8 +678,8 @@ __global__ __launch_bounds__(kThreads) void shared_kernel(const KArgs a, int jw)
 // Jobs with trace segments of their own, one per wavefront at a time: slot ->
 // job through a.order where it is set; with a.next_slot (0 at launch) the
 // wavefronts take slots in turn until none is left, otherwise wavefront w of
-// the launch runs slot w.  Slots from J on are the jobs with a row, once more
-// for the row alone.
+// the launch runs slot w.  With rows_apart the first slots are the jobs with a
+// row, for the row alone; otherwise a job's wavefront writes its row too.
 template <int W, int SMAX>
 __global__ __launch_bounds__(kThreads) void seg_kernel(const KArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -635,19 +689,18 @@ __global__ __launch_bounds__(kThreads) void seg_kernel(const KArgs a) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   unsigned char* rec = smem + tab + (size_t)wave * lean_wave_lds(W, a.M, SMAX, false);
-  const int64_t n_rows = a.finish_stride > 0 ? a.n_finish : 0;
   auto take_slot = [&]() -> int64_t {
     int v = 0;
     if (lane == 0) v = atomicAdd(a.next_slot, 1);
     return (int64_t)__builtin_amdgcn_readfirstlane(v);
   };
   int64_t slot = a.next_slot ? take_slot() : (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
-  while (slot < a.J + n_rows) {
-    // the row slots come first: a row job's chain is as long as the job's own
-    const bool rows = slot < n_rows;
-    const int64_t s = slot - n_rows;
-    const int64_t job = rows ? (int64_t)a.finish_jobs[slot]
-                             : a.order ? (int64_t)__builtin_amdgcn_readfirstlane(a.order[s]) : s;
+  const int64_t apart = a.rows_apart ? a.n_finish : 0;
+  while (slot < apart + a.J) {
+    const bool again = slot < apart;
+    const int64_t s = slot - apart;
+    const int64_t job = again ? (int64_t)a.finish_jobs[slot]
+                              : a.order ? (int64_t)__builtin_amdgcn_readfirstlane(a.order[s]) : s;
     int p = 0;
     double sigma = 0.0;
     int64_t begin = 0, len = 0;
@@ -661,17 +714,24 @@ __global__ __launch_bounds__(kThreads) void seg_kernel(const KArgs a) {
     in.n = len;
     in.jw = 1;
     in.sigma = sigma;
-    in.row = rows ? a.out_finish + slot * a.finish_stride : nullptr;
     in.row_n = len < a.finish_stride ? len : a.finish_stride;
-    in.digest = !rows && a.out_digest != nullptr;
+    in.row_slot = 0;
+    const int f = again ? (int)slot
+                        : apart || in.row_n <= 0 ? -1 : lean_row(a, a.n_finish, [&](int j) { return j == job; });
+    in.row = f >= 0 ? a.out_finish + f * a.finish_stride : nullptr;
+    in.digest = !again && a.out_digest != nullptr;
+    if (again && in.n > in.row_n) in.n = in.row_n;  // the row needs no more requests
     in.cfg = lane < a.G ? a.group_cfg[(int64_t)p * a.G + lane] : -1;
     if (in.cfg >= a.C || in.cfg < 0) in.cfg = -1;
     in.hm = (lane < a.M ? a.host_mask[(int64_t)p * a.M + lane] : 0) & __builtin_amdgcn_ballot_w64(in.cfg >= 0);
-    if (rows) {
-      if (in.n > in.row_n) in.n = in.row_n;  // the row needs no more requests
-      (void)lean_go<W, SMAX, false, true>(a, in, sL, lshift, rec, nullptr);
+    if (again) {
+      (void)lean_go<W, SMAX, false, 2>(a, in, sL, lshift, rec, nullptr);
     } else {
-      const LeanOut o = lean_go<W, SMAX, false, false>(a, in, sL, lshift, rec, nullptr);
+      LeanOut o;
+      if (in.row)
+        o = lean_go<W, SMAX, false, 1>(a, in, sL, lshift, rec, nullptr);
+      else
+        o = lean_go<W, SMAX, false, 0>(a, in, sL, lshift, rec, nullptr);
       if (lane == 0) {
         a.out_served[job] = o.served;
         if (a.out_attain) a.out_attain[job] = len > 0 ? (double)o.served / (double)len : 0.0;

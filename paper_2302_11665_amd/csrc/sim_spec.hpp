@@ -167,7 +167,7 @@ __device__ __forceinline__ int fix_segment(const SpecArgs& a, const LeanWave<W, 
     mn = a.model[ahead < e ? ahead : top];
     int rank, nh;
     const bool mine = lean_mine<W, SMAX>(w, cb + lane < e, mv, rank, nh);
-    uint64_t word = lean_uniform(lean_chunk<W, SMAX, UNI, false, false>(st, w, tv, mv, mine, rank, nh));
+    uint64_t word = lean_uniform(lean_chunk<W, SMAX, UNI, false, 0>(st, w, tv, mv, mine, rank, nh));
     served += __builtin_popcountll(word);
     word = __builtin_amdgcn_ballot_w64(mine && ((word >> rank) & 1u));
     if (lane == 0) a.bitmap[(cb >> 6) * J + job] = word;

@@ -108,6 +108,41 @@ def test_many_scales_on_few_placements(api, G, P, per_simd, mixes):
                                                   *pb.finish_jobs.tolist()}))
 
 
+@pytest.mark.parametrize("G,P,scales,rows", [
+    (1, 4100, [3.0], [0, 1, 2, 63, 64, 4099]), (4, 3001, [2.0], [5, 1, 2998, 3000, 6]), (16, 2051, [4.0], [2, 3, 0, 1, 2050]),
+    (16, 2049, [1.0, 6.0], [1, 3, 4096, 4097, 0]), (5, 1, np.geomspace(0.5, 20.0, 2100).tolist(), [0, 1, 7, 2099, 1050]),
+    (32, 2100, [2.0], [1, 0, 2099]), (64, 1500, [2.0], [1499, 3, 0])])
+def test_rows_of_jobs_that_share_a_wavefront(api, G, P, scales, rows):
+    """Rows of several jobs of one wavefront, of its first and its last job, of a
+    job that hosts less than the others, in any order, at one and at many scales."""
+    pb = _problem(G + P, 200, G, P, scales, hosts=2)
+    pb = dataclasses.replace(pb, finish_jobs=np.array(rows, np.int32))
+    J = P * len(scales)
+    _check(api, pb, f"rows G={G} P={P} K={len(scales)}", sorted({*range(0, J, 97), *rows}))
+
+
+def test_rows_do_not_lengthen_full_launches(api):
+    """Two wavefronts on every SIMD: a few rows are written by the wavefronts that
+    simulate their jobs anyway (wavefronts of their own took 1.4 times the time)."""
+    import torch
+    P = 8 * torch.cuda.get_device_properties(0).multi_processor_count
+    pb = _problem(3, 5000, 64, P, [2.0], cfgs=((1, 1),))
+    best = []
+    for fin in ([], [0, P // 3, P // 2, P - 1]):
+        dp = api.upload(dataclasses.replace(pb, finish_jobs=np.array(fin, np.int32)))
+        t = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            api.run(dp)
+            b.record()
+            torch.cuda.synchronize()
+            t.append(a.elapsed_time(b))
+        best.append(min(t))
+    say("rows on full SIMDs: ms without and with", best)
+    assert best[1] < 1.2 * best[0], best
+
+
 def test_infinite_finish_times(api):
     _check(api, _problem(5, 300, 12, 4, [1.0, np.inf], big=True), "infinite finish times")
 
