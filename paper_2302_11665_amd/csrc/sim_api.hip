@@ -151,10 +151,11 @@ bool lean_mixes_scales(int W, int64_t J, int64_t K, int jw) {
 }
 
 // Which calls the group-per-lane kernels take, by their stage-latency tables:
-// the sizes these calls have always been taken up to (the table, the model
-// records of four wavefronts and a staged chunk of 2048, or of four times 256,
-// requests in a workgroup's LDS); larger ones go to the general kernel, or are
-// refused, as before.  The kernels themselves need less.
+// the sizes these calls have always been taken up to (the table, 32 to 128 bytes
+// a model for four wavefronts and a staged chunk of 2048, or of four times 256,
+// requests in a workgroup's LDS).  Larger ones are refused, as they always have
+// been: the general kernel takes tables of 64 KB at most, all of them among
+// these.  The kernels themselves need less.
 bool lean_takes(const KArgs& a, int smax, int chunk = 2048) {
   const size_t records = (size_t)as_dev::kWaves * a.M * ((size_t)1 << as_dev::rec_shift(smax));
   return records + (size_t)a.M * pow2ceil(a.C) * smax * 8 + (size_t)chunk * 20 <= shared_lds_limit();

@@ -9,45 +9,44 @@ import numpy as np
 import pytest
 
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
-from gpu_common import compare, oracle_problem, say  # noqa: E402
+from gpu_common import compare, kernels_run, oracle_problem, say  # noqa: E402
 from oracle_pins import random_case  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
 
 # kernel selections the library offers (environment variables read per call):
-# the shared-trace kernel (one group per lane), the general LDS-staged kernel
+# the group-per-lane kernels, the general LDS-staged kernel
 # with one or two groups per lane, and the segment-speculative kernels
+NEVER_GIVE_UP = {"ALPASERVE_SPEC_CAP": str(1 << 40)}
 VARIANTS = {
     "shared": {"ALPASERVE_PATH": "shared"},
     "lds": {"ALPASERVE_PATH": "lds", "ALPASERVE_GPL": "1"},
     "lds_gpl2": {"ALPASERVE_PATH": "lds", "ALPASERVE_GPL": "2"},
     # one lane per job over trace segments run at once and reconciled: the
     # default segment count, an odd count, and 64 segments (short and empty
-    # segments whose states never meet: many reconciliation rounds)
+    # segments whose states never meet: many reconciliation rounds).  A cap on
+    # one re-run's requests replaces the fix-ups' own limits, which would leave
+    # most of these short traces to the fallback kernels.
     "spec": {"ALPASERVE_PATH": "spec"},
-    "spec_seg7": {"ALPASERVE_PATH": "spec", "ALPASERVE_SPEC_SEGMENTS": "7"},
-    "spec_seg64": {"ALPASERVE_PATH": "spec", "ALPASERVE_SPEC_SEGMENTS": "64"},
+    "spec_seg7": {"ALPASERVE_PATH": "spec", "ALPASERVE_SPEC_SEGMENTS": "7", **NEVER_GIVE_UP},
+    "spec_seg64": {"ALPASERVE_PATH": "spec", "ALPASERVE_SPEC_SEGMENTS": "64", **NEVER_GIVE_UP},
     # no warm-up: every segment starts from the empty state
-    "spec_seg7_cold": {"ALPASERVE_PATH": "spec", "ALPASERVE_SPEC_SEGMENTS": "7", "ALPASERVE_SPEC_WARMUP": "0"},
+    "spec_seg7_cold": {"ALPASERVE_PATH": "spec", "ALPASERVE_SPEC_SEGMENTS": "7", "ALPASERVE_SPEC_WARMUP": "0",
+                       **NEVER_GIVE_UP},
     # a warm-up shorter than a segment
     "spec_seg16_warm100": {"ALPASERVE_PATH": "spec", "ALPASERVE_SPEC_SEGMENTS": "16",
-                           "ALPASERVE_SPEC_WARMUP": "100"},
-    # reconciliation rounds on the one-lane-per-job kernel (the default takes the
-    # group-per-lane kernel for jobs of at most 16 groups)
-    "spec_seg7_lanerounds": {"ALPASERVE_PATH": "spec", "ALPASERVE_SPEC_SEGMENTS": "7", "ALPASERVE_SPEC_WARMUP": "0",
-                             "ALPASERVE_SPEC_ROUNDS": "lane"},
+                           "ALPASERVE_SPEC_WARMUP": "100", **NEVER_GIVE_UP},
     # saved states every 64 requests: re-runs stop at the first one they meet
     "spec_seg5_ck64": {"ALPASERVE_PATH": "spec", "ALPASERVE_SPEC_SEGMENTS": "5", "ALPASERVE_SPEC_WARMUP": "0",
-                       "ALPASERVE_SPEC_CKPT": "64"},
+                       "ALPASERVE_SPEC_CKPT": "64", **NEVER_GIVE_UP},
     # re-runs give up after 64 requests without meeting the old results (cold
-    # segments rarely meet that soon): the shared-trace kernels launched behind
-    # the pipeline, gated on that flag, produce the results; with either
-    # round kernel
+    # segments rarely meet that soon): the group-per-lane kernels launched behind
+    # the pipeline, gated on that flag, produce the results
     "spec_seg7_giveup": {"ALPASERVE_PATH": "spec", "ALPASERVE_SPEC_SEGMENTS": "7", "ALPASERVE_SPEC_WARMUP": "0",
                          "ALPASERVE_SPEC_CAP": "64"},
-    "spec_seg7_giveup_lane": {"ALPASERVE_PATH": "spec", "ALPASERVE_SPEC_SEGMENTS": "7",
-                              "ALPASERVE_SPEC_WARMUP": "0", "ALPASERVE_SPEC_CAP": "64", "ALPASERVE_SPEC_ROUNDS": "lane"},
+    # cold segments under the fix-ups' own limits
+    "spec_seg7_cold_limits": {"ALPASERVE_PATH": "spec", "ALPASERVE_SPEC_SEGMENTS": "7", "ALPASERVE_SPEC_WARMUP": "0"},
 }
 
 
@@ -64,12 +63,29 @@ def gpu_api():
 @pytest.fixture(params=sorted(VARIANTS))
 def gpu(request, gpu_api, monkeypatch):
     for k in ("ALPASERVE_PATH", "ALPASERVE_GPL", "ALPASERVE_SPEC_SEGMENTS", "ALPASERVE_SPEC_WARMUP",
-              "ALPASERVE_SPEC_CKPT", "ALPASERVE_SPEC_ROUNDS", "ALPASERVE_SPEC_CAP"):
+              "ALPASERVE_SPEC_CKPT", "ALPASERVE_SPEC_CAP"):
         monkeypatch.delenv(k, raising=False)
     for k, v in VARIANTS[request.param].items():
         monkeypatch.setenv(k, v)
     say("variant", request.param)
     return gpu_api
+
+
+def test_variants_reach_the_kernels_they_name(gpu_api, monkeypatch):
+    """The variants that are there for the fix-ups finish on them, and the one
+    that is there for the fallback ends on the kernels behind the gate."""
+    from paper_2302_11665_amd.workload import problems
+    pb = problems.c4_heavy(duration=60.0, n_placements=64, n_finish=2)
+    for name, env in sorted(VARIANTS.items()):
+        if env.get("ALPASERVE_PATH") != "spec" or "ALPASERVE_SPEC_CAP" not in env:
+            continue
+        with monkeypatch.context() as mp:
+            for k, v in env.items():
+                mp.setenv(k, v)
+            times = kernels_run(lambda: gpu_api.simulate_problem(pb))
+        gated = sum(t for n, t in times.items() if "shared_kernel" in n)
+        say("variant", name, "gated kernels", round(gated, 1), "us")
+        assert any("spec_pass0" in n for n in times) and (gated > 1000.0) == (name == "spec_seg7_giveup"), (name, times)
 
 
 def test_c1_all_placements(gpu):
