@@ -178,12 +178,14 @@ def test_batching_every_lane_twice(dev):
 
 
 @pytest.mark.parametrize("G,Smax,M,C,P,B", [(2, 1, 2, 1, 3, 1), (2, 2, 3, 2, 3, 33), (3, 8, 64, 16, 4, 40),
-                                            (20, 2, 64, 2, 4, 5), (4, 1, 64, 1, 1300, 7)])
+                                            (20, 2, 64, 2, 4, 5), (4, 1, 64, 1, 1300, 7), (4, 1, 64, 1, 2100, 7),
+                                            (9, 4, 64, 8, 1400, 4)])
 def test_batching_queues_past_the_ring(dev, G, Smax, M, C, P, B):
     """Bursts on a few of the models, so that their queues grow past the 8 to
     32 entries kept in LDS and are served, and dropped, from both sides of
     that line: few models, a large latency table, 64 models on 20 groups, and
-    so many jobs that the rings are at their smallest."""
+    so many jobs that the rings are at their smallest, or none where they would
+    keep jobs from being resident."""
     rng = np.random.default_rng(7000 + M * 31 + G)
     n = 700 if P < 100 else 260
     t = np.sort(np.concatenate([np.repeat(rng.uniform(0.0, 20.0, 2), n // 4), rng.uniform(0.0, 30.0, n - 2 * (n // 4))]))
