@@ -99,8 +99,9 @@ typedef struct {
  *   finish_jobs      HOST [n_finish] distinct job ids in [0, J), or NULL
  *   out_finish       [n_finish][trace->n] per-request outputs of those jobs
  * Each job's state lives in one wavefront: lanes hold the groups of a job
- * (several jobs per wavefront when the group count allows), arrivals are
- * staged through LDS in chunks shared by the workgroup.
+ * (several jobs per wavefront when the group count allows), and every wavefront
+ * stages its requests through LDS, 64 at a time.  Long traces are cut into
+ * segments that run at the same time where that pays (one lane per job).
  */
 int as_simulate_placements(const as_trace_t* trace, const as_models_t* models,
                            const as_placements_t* placements, const double* slo_scale,

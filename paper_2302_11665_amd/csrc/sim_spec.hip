@@ -868,8 +868,8 @@ namespace {
 
 // Warm-up requests before a segment.  A shorter warm-up leaves more start
 // states wrong, a longer one is simulated for nothing (1000 placements, 900,000
-// requests, 64 segments: 4096 -> 12.2 ms, 8192 -> 11.3, 16384 -> 12.5, and on
-// another seed, whose runs meet later, 99, 31 and 29).
+// requests, 64 segments, one seed: 4096 -> 12.2 ms, 8192 -> 11.3, 16384 -> 12.5,
+// and on another, whose runs meet later, 99, 31 and 29).
 constexpr int64_t kSpecWarmup = 8192;
 // Requests per segment at least: beyond this the warm-up is nearly all of pass
 // 0 (1000 placements, 200,000 requests: segments of 12,500 8.0 ms, 6250 7.2,
@@ -967,12 +967,13 @@ double lean_ns(const KArgs& k, int smax) {
 // call, by a model in nanoseconds of one wavefront: a request of pass 0, with 64
 // jobs, 150 + 35 per stage (287 at 4 stages), over a segment and its warm-up; the
 // fix-ups are taken as 2 ms.  The speculative kernels must promise 0.4 of the
-// other time, because traffic under which runs do not meet costs both: 777
-// late selections of 32 two-stage groups, 76,801 requests, promise 0.64 and do
-// not meet, which took 11.1 ms against 7.2 on the group-per-lane kernels alone.
-// Measured at 1000 placements and 4 stages, which promise 0.1 and 0.3: 900,000
-// requests 11.3 ms against 93.6, 200,000 6.5 against 20.7.  A single segment
-// never pays.
+// other time, because traffic under which runs do not meet costs both.  Measured
+// on 16 four-stage groups, where runs meet / do not / the group-per-lane kernels
+// alone: promise 0.08 (1000 placements, 900,000 requests) 11 to 79 / 88 to 105 /
+// 83 to 93 ms; 0.34 (8000, 500,000) 31 / 86 to 97 / 70; 0.39 (8000, 300,000) 18 /
+// 53 to 59 / 42; 0.43 (4000, 214,000) 9 to 20 / 25 to 29 / 20; 0.55 (1000, 99,000)
+// 7 to 9 / 12 to 13 / 9; 0.64 (777 late selections of 32 two-stage groups, 76,801
+// requests) - / 11 / 7.  A single segment never pays.
 bool spec_pays(const KArgs& k, int smax, int nseg, int jpw, int per_cu) {
   if (nseg < 2) return false;
   const double slots = (double)compute_units() * std::max(per_cu, 1);

@@ -87,11 +87,12 @@ __device__ __forceinline__ int spec_ckpts(int64_t b, int64_t e, int64_t ck) { re
 //
 // One job per wavefront on the group-per-lane step (sim_lean.hpp), whose
 // request is the shortest chain: a round's time is its longest re-run.
-// Measured: 1000 placements, 900,000 requests, 53.2 -> 17.1 ms a call (64
-// segments of 14,062 requests, where rounds of one segment after the other's
-// end, each on all jobs' lanes, had held it to 6); 8192 placements, 3.6 M
-// requests, on a seed where some jobs' runs never meet: 735 ms, since one of
-// them sent the whole call to the other kernels, -> 164 to 182.
+// Measured: 1000 placements, 900,000 requests, 13 seeds: 12 to 79 ms a call (105
+// where the fix-ups gave up; 64 segments of 14,062 requests), 48 to 205 with the
+// six segments to which rounds of one segment after the other's end, each on all
+// jobs' lanes, had held it; 8192 placements, 3.6 M requests, on a seed where some
+// jobs' runs never meet: 735 ms, since one of them sent the whole call to the
+// other kernels, -> 164 to 182.
 //
 // The re-run of one segment.  Returns 0: gave up; 1: met the old results; 2: ran
 // to the end, which st.F holds.  first: entries of the first list in round 1,
