@@ -61,20 +61,21 @@ KERNEL_SOURCES = ["paper_2302_11665_amd/csrc/sim_api.hip", "paper_2302_11665_amd
                   "paper_2302_11665_amd/csrc/sim_lean.hpp", "paper_2302_11665_amd/csrc/sim_shared.hpp",
                   "paper_2302_11665_amd/csrc/sim_spec.hip", "paper_2302_11665_amd/csrc/sim_spec.hpp"]
 MEASURED_TRAFFIC = {
-    "sources_sha256": "684637c3137697b219070a57f8d6c86345014f155cb72e55f014cddc6114a889",
+    "sources_sha256": "bd9d6961c821d1e2a4ef2a0b78d9897b8644bbfcdc99b4bb5e742d92acede9fb",
     # one step of the heavy-trace workload runs the segment-speculative
-    # pipeline (configuration check, pass 0, reconciliation rounds, output
-    # rows, digest): its counters summed over the step's dispatches
-    "kernel": "spec_pass0<4, 32, true, 64, true> + spec_round_fast<16, 4> + spec_rows<4, 32, true, 64> "
+    # pipeline (configuration check, pass 0, the list of wrong segments and
+    # the fix-ups, output rows, digest): its counters summed over the step's
+    # dispatches
+    "kernel": "spec_pass0<4, 32, true, 64, true> + spec_list + spec_fix<16, 4> + spec_rows<4, 32, true, 64> "
               "(row pieces and the final step) + spec_cfg_check (+ the variants that return at once)",
-    "fetch_kib": 2218171.63, "write_kib": 5990707.06,
-    "fetch_scale": 1048576.0 / 524301.90, "write_scale": 1048576.0 / 1048576.0,
+    "fetch_kib": 2093762.69, "write_kib": 5991603.10,
+    "fetch_scale": 1048576.0 / 524301.98, "write_scale": 1048576.0 / 1048576.0,
 }
 MEASURED_TRAFFIC_SWEEP = {
-    "sources_sha256": "684637c3137697b219070a57f8d6c86345014f155cb72e55f014cddc6114a889",
-    "kernel": "seg_kernel<1>",
-    "fetch_kib": 2595524.38, "write_kib": 14218.69,
-    "fetch_scale": 1048576.0 / 524301.90, "write_scale": 1048576.0 / 1048576.0,
+    "sources_sha256": "bd9d6961c821d1e2a4ef2a0b78d9897b8644bbfcdc99b4bb5e742d92acede9fb",
+    "kernel": "seg_kernel<64, 1>",
+    "fetch_kib": 2595482.31, "write_kib": 14207.0,
+    "fetch_scale": 1048576.0 / 524301.98, "write_scale": 1048576.0 / 1048576.0,
 }
 
 
@@ -601,7 +602,7 @@ def main():
             "algorithmic_bytes": int(algorithmic_bytes(pb)),
             "ops_per_event": round(ops / events, 3),
             "note": "fp64 lane-ops (max/add/cmp/mul, no FMA) of the definition per step / mean step time; "
-                    "the step is the speculative pipeline (pass 0, reconciliation rounds, digest); "
+                    "the step is the speculative pipeline (pass 0, fix-ups, output rows and digest); "
                     "traffic includes its workspace (accept bitmap, checkpoints)"}
 
     out = {"metric": METRIC, "value": round(value, 1), "unit": "events/s", "n_gpus": 1,
