@@ -93,11 +93,23 @@ __device__ __forceinline__ int spec_ckpts(int64_t b, int64_t e, int64_t ck) { re
 // jobs' lanes, had held it; 8192 placements, 3.6 M requests, on a seed where some
 // jobs' runs never meet: 735 ms, since one of them sent the whole call to the
 // other kernels, -> 164 to 182.
-//
+
+// Counts requests that a re-run has simulated; whether that is more than the
+// fix-ups may.  first: entries of the first list in round 1, else 0 (that
+// round's entries promise what those taken so far have run, the ones that still
+// run in part, so the promise is never too high).
+__device__ __forceinline__ bool fix_spent(const SpecArgs& a, int64_t requests, int first) {
+  unsigned long long all = 0;
+  if ((threadIdx.x & 63) == 0) all = atomicAdd(a.work, (unsigned long long)requests);
+  all = lean_uniform(all);
+  if (all > (unsigned long long)a.budget) return true;
+  if (first == 0) return false;
+  const int taken = __hip_atomic_load(a.taken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return (double)all * first > (double)a.budget1 * (taken < first ? taken : first);
+}
+
 // The re-run of one segment.  Returns 0: gave up; 1: met the old results; 2: ran
-// to the end, which st.F holds.  first: entries of the first list in round 1,
-// else 0 (that round's entries promise what those taken so far have run, the
-// ones that still run in part, so the promise is never too high).
+// to the end, which st.F holds.
 template <int W, int SMAX, bool UNI>
 __device__ __forceinline__ int fix_segment(const SpecArgs& a, const LeanWave<W, SMAX>& w, LeanLane<SMAX>& st,
                                            int job, int k, const double (&start)[SMAX], int first) {
@@ -147,18 +159,11 @@ __device__ __forceinline__ int fix_segment(const SpecArgs& a, const LeanWave<W, 
       if (mine_g)
 #pragma unroll
         for (int s = 0; s < SMAX; ++s) a.ckpt[at + (size_t)s * J] = st.F[s];
-      unsigned long long all = 0;
       if (lane == 0) {
         a.ck_served[cj] = served;
         a.ck_fsum[cj] = fsum;
-        all = atomicAdd(a.work, (unsigned long long)a.ck);
       }
-      all = lean_uniform(all);
-      if (all > (unsigned long long)a.budget) return 0;
-      if (first > 0) {
-        const int taken = __hip_atomic_load(a.taken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if ((double)all * first > (double)a.budget1 * (taken < first ? taken : first)) return 0;
-      }
+      if (fix_spent(a, a.ck, first)) return 0;
     }
     if (cb - b >= a.cap) return 0;
     const double tv = tn;
@@ -173,6 +178,8 @@ __device__ __forceinline__ int fix_segment(const SpecArgs& a, const LeanWave<W, 
     word = __builtin_amdgcn_ballot_w64(mine && ((word >> rank) & 1u));
     if (lane == 0) a.bitmap[(cb >> 6) * J + job] = word;
   }
+  // what lies behind the last saved state, in a short segment all of it
+  if (fix_spent(a, e - b - (int64_t)nck * a.ck, first)) return 0;
   const uint64_t fsum = seg_sum_u64<64>(st.fin);
   if (lane == 0) {
     a.seg_served[(size_t)k * J + job] = served;

@@ -118,3 +118,18 @@ def test_when_the_fix_ups_give_up(sim, monkeypatch, kind, seconds, P, stretch, g
         s, dg, _ = oracle.lib().simulate_job(pb.t, pb.model, pb.d_single, pb.cfg_stages, pb.stage_lat,
                                              pb.group_cfg[j], pb.host_mask[j], pb.slo_scale[0])
         assert int(got[0][j]) == s and tuple(int(x) for x in got[2][j]) == dg, j
+
+
+def test_short_segments_count_as_work(sim, monkeypatch):
+    """98 segments of 2048 requests, as far apart as the saved states, so that
+    none lies inside a segment: the first round's re-runs still count, and the
+    fix-ups end before they have run them all (24,000 x 2048 requests are 0.21
+    of the time that the group-per-lane kernels take)."""
+    for v in ("PATH", "SPEC_SEGMENTS", "SPEC_WARMUP", "SPEC_CAP", "SPEC_CKPT", "SPEC_MAX_WORKSPACE"):
+        monkeypatch.delenv("ALPASERVE_" + v, raising=False)
+    pb = _traffic("additions", 214.0, 600, 1.02)
+    pb.t, pb.model = pb.t[:98 * 2048], pb.model[:98 * 2048]
+    say(f"fix-ups, short segments: {pb.n_jobs} jobs x {len(pb.t)} requests")
+    times = kernels_run(lambda: _run(sim, pb))
+    fix, gated = (sum(t for n, t in times.items() if x in n) for x in ("spec_fix", "shared_kernel"))
+    assert gated > 1000.0 and 0.0 < fix < 0.12 * gated, times
