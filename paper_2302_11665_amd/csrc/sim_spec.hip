@@ -889,16 +889,25 @@ constexpr int64_t kSpecCheckpointBytes = 512ll << 20;
 //     were worth finishing took 0.05 to 0.15 in the first round and up to 0.3 in
 //     all, the others 0.22 to 8 in the first round;
 //   * at once where more than kSpecPairs of all segments start wrong (worth
-//     finishing: up to 0.45), or more than kSpecAgain of them again after the
-//     first round, so that the rounds leave most of the trace to the job-by-job
-//     step (300 jobs, 200,000 requests: 0.71 and 0.73 took 13 and 15 ms, 0.80
-//     took 31, where the group-per-lane kernels take 18).
+//     finishing: up to 0.45);
+//   * after the first round, where more than kSpecAgain of the segments that it
+//     took are listed again, so that the rounds leave most of the trace to the
+//     job-by-job step (300 jobs, 200,000 requests: 0.71 and 0.73 took 13 and 15
+//     ms, 0.80 took 31, where the group-per-lane kernels take 18); kSpecAgainSome
+//     where they were at most kSpecSome of all segments, and never where they
+//     were at most kSpecFew, since the few jobs then left cost no more than
+//     giving up (20 to 1200 jobs of 132,000 to 914,000 requests, finished / given
+//     up in ms: share 0.02 to 0.08 at 0.79 to 0.995 listed again 18.5 / 60, 38 /
+//     105, 40 / 71, 20 / 26 and level on three others; 0.19 at 0.87 and 0.93 45 /
+//     58 and 24 / 36; 0.12 to 0.23 at 0.93 to 0.995 30 / 25, 41 / 28, 52 / 34, 62
+//     / 45; 0.27 to 0.4 at 0.84 to 0.92 65 / 53, 46 / 41, 47 / 40).
 // Measured, giving up and finished: 1000 placements of 16 four-stage groups,
 // 900,000 requests, seven seeds and loads 91 to 108 and 22 to 78 ms; 4000 of
 // them 106 and 37; 300,000 requests 36 and 17; and where groups stay saturated
 // 88 and 108 to 545.
 constexpr double kSpecTotal = 1.0 / 3.0, kSpecFirst = 0.18, kSpecFixNs = 90.0;
 constexpr double kSpecPairs = 0.5, kSpecAgain = 0.75;
+constexpr double kSpecFew = 0.1, kSpecSome = 0.25, kSpecAgainSome = 0.93;
 
 }  // namespace
 
@@ -1133,20 +1142,23 @@ int run_spec(KArgs& k, int smax, hipStream_t stream, bool can_give_up, void* cal
   a.ck = pl.ck;
   a.ckps = (int32_t)pl.ckps;
   a.cap = INT64_MAX;
-  a.budget = a.budget1 = a.pairs = INT64_MAX;
-  a.again = 2.0;  // never
+  a.budget = a.budget1 = a.pairs = a.few = a.some = INT64_MAX;  // never
+  a.again = a.again_some = 1.0;
   if (can_give_up) {
     const double all = lean_ns(k, smax) * 4 * compute_units() / kSpecFixNs;
     a.budget = (int64_t)(kSpecTotal * all);
     a.budget1 = (int64_t)(kSpecFirst * all);
-    a.pairs = (int64_t)(kSpecPairs * (double)k.J * (a.nseg - 1));
+    const double starts = (double)k.J * (a.nseg - 1);
+    a.pairs = (int64_t)(kSpecPairs * starts);
+    a.few = (int64_t)(kSpecFew * starts);
+    a.some = (int64_t)(kSpecSome * starts);
     a.again = kSpecAgain;
+    a.again_some = kSpecAgainSome;
   }
   // ALPASERVE_SPEC_CAP (requests of one re-run) alone decides where it is set (tests)
   if (const char* c = getenv("ALPASERVE_SPEC_CAP"); c && can_give_up) {
     a.cap = std::max<int64_t>(64, atoll(c));
-    a.budget = a.budget1 = a.pairs = INT64_MAX;
-    a.again = 2.0;
+    a.budget = a.budget1 = a.pairs = a.few = a.some = INT64_MAX;
   }
   if ((int64_t)a.njb * a.nseg > 0x7FFFFFFFLL) return AS_E_LIMITS;
   a.nw = (k.n + 63) / 64;

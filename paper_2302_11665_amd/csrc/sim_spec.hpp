@@ -52,7 +52,8 @@ struct SpecArgs {
   int64_t budget;       // and all of them together
   int64_t budget1;      // and those of round 1, by what its entries promise so far
   int64_t pairs;        // entries of the first list beyond which they give up at once
-  double again;         // and share of it listed again beyond which they do
+  int64_t few, some;    // and shares of it listed again beyond which they do: none up to few
+  double again_some, again;  // entries, again_some up to some, else again
   int64_t nw;
   int64_t warmup;  // requests simulated before a segment to estimate its start state
   int32_t M, C, smax_in, G, K, J, n_finish, nseg, njb;
@@ -261,7 +262,12 @@ __global__ __launch_bounds__(64) void spec_fix(const SpecArgs a, int q) {
   const int n = __builtin_amdgcn_readfirstlane(a.count[q - 1]);
   if (n == 0 || __builtin_amdgcn_readfirstlane(a.cfg_info[2]) != 0) return;
   const int lane = threadIdx.x & 63;
-  if ((q == 1 && n > a.pairs) || (q == 2 && n > a.again * a.count[0])) {
+  bool over = q == 1 && n > a.pairs;
+  if (q == 2) {
+    const int first = a.count[0];
+    over = first > a.few && n > (first > a.some ? a.again : a.again_some) * first;
+  }
+  if (over) {
     if (blockIdx.x == 0 && lane == 0) a.cfg_info[2] = 1;
     return;
   }

@@ -100,6 +100,7 @@ def _traffic(kind, seconds, P, stretch):
     ("additions", 214.0, 1000, 1.02, True),    # by the first round's requests
     ("two replicas", 143.0, 300, 1.1, True),   # by what the first round lists again
     ("two replicas", 214.0, 1000, 1.1, True),  # by all rounds' requests
+    ("two replicas", 430.0, 24, 1.6, False),   # one segment is wrong, and its successor
 ])
 def test_when_the_fix_ups_give_up(sim, monkeypatch, kind, seconds, P, stretch, gives_up):
     for v in ("PATH", "SPEC_SEGMENTS", "SPEC_WARMUP", "SPEC_CAP", "SPEC_CKPT", "SPEC_MAX_WORKSPACE"):
