@@ -285,11 +285,16 @@ __device__ __forceinline__ void lean_steps(LeanLane<SMAX>& st, const LeanReq<SMA
 // accepted by this lane).  A wavefront that writes a row beside its results reads
 // them by halves at 2 and 4 stages: all at once, its registers (134 and 170, not
 // 124 and 160) would take a wavefront from every SIMD, also without rows (16,384
-// jobs of 16 four-stage groups: 5.4 ms instead of 5.2).
+// jobs of 16 four-stage groups: 5.4 ms instead of 5.2).  So does one with the
+// statistics of 33 to 64 groups of differing depths: with all eight requests in
+// registers the compiler leaves the chain behind the minimum instead of between
+// its steps (2 and 4 stages, 15,000 requests: 2.05 and 2.34 ms, 1.83 and 1.99 by
+// halves; elsewhere halves are up to 4 % slower or the same).
 template <int W, int SMAX, bool UNI, bool STATS, int ROW, bool MS>
 __device__ __forceinline__ uint32_t lean_batch(LeanLane<SMAX>& st, const unsigned char* r, const char* lrow,
                                                uint32_t blo, uint32_t bhi, uint32_t orow) {
-  constexpr int N = ROW == 1 && (SMAX == 2 || SMAX == 4) ? kLeanB / 2 : kLeanB;
+  constexpr bool kHalves = ROW == 1 || (STATS && W == 64 && !UNI);
+  constexpr int N = kHalves && (SMAX == 2 || SMAX == 4) ? kLeanB / 2 : kLeanB;
   uint32_t sr = 0;
   {
     LeanReq<SMAX> q[N];

@@ -54,7 +54,7 @@ def _stats_case(rng, G, Smax, M, n):
 
 # the group-per-lane kernels' statistics mode, with one scale and with several
 @pytest.mark.parametrize("one_scale", [True, False])
-@pytest.mark.parametrize("G,Smax", [(1, 1), (3, 2), (16, 4), (17, 3), (40, 8), (64, 1)])
+@pytest.mark.parametrize("G,Smax", [(1, 1), (3, 2), (16, 4), (17, 3), (40, 8), (64, 1), (33, 2), (64, 4)])
 def test_stats_kernel_matches_oracle(dev, G, Smax, one_scale):
     import torch
     rng = np.random.default_rng(100 + G * 10 + Smax)
