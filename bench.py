@@ -61,20 +61,20 @@ KERNEL_SOURCES = ["paper_2302_11665_amd/csrc/sim_api.hip", "paper_2302_11665_amd
                   "paper_2302_11665_amd/csrc/sim_lean.hpp", "paper_2302_11665_amd/csrc/sim_shared.hpp",
                   "paper_2302_11665_amd/csrc/sim_spec.hip", "paper_2302_11665_amd/csrc/sim_spec.hpp"]
 MEASURED_TRAFFIC = {
-    "sources_sha256": "85d1f8ac894b125cbf43ddabeda6db2de3069aae9b5e558c4ae21509a284294a",
+    "sources_sha256": "7248bf29923cc8a9e079eef40b9c29b49aa4db561f914cd93577d6af19e19273",
     # one step of the heavy-trace workload runs the segment-speculative
     # pipeline (configuration check, pass 0, the list of wrong segments and
     # the fix-ups, output rows, digest): its counters summed over the step's
     # dispatches
     "kernel": "spec_pass0<4, 32, true, 64, true> + spec_list + spec_fix<16, 4> + spec_rows<4, 32, true, 64> "
               "(row pieces and the final step) + spec_cfg_check (+ the variants that return at once)",
-    "fetch_kib": 2093858.63, "write_kib": 5991654.03,
+    "fetch_kib": 2093496.25, "write_kib": 5991569.47,
     "fetch_scale": 1048576.0 / 524301.98, "write_scale": 1048576.0 / 1048576.0,
 }
 MEASURED_TRAFFIC_SWEEP = {
-    "sources_sha256": "85d1f8ac894b125cbf43ddabeda6db2de3069aae9b5e558c4ae21509a284294a",
+    "sources_sha256": "7248bf29923cc8a9e079eef40b9c29b49aa4db561f914cd93577d6af19e19273",
     "kernel": "seg_kernel<64, 1>",
-    "fetch_kib": 2595493.63, "write_kib": 14204.91,
+    "fetch_kib": 2595508.38, "write_kib": 14207.66,
     "fetch_scale": 1048576.0 / 524301.98, "write_scale": 1048576.0 / 1048576.0,
 }
 
